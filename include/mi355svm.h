@@ -108,7 +108,14 @@ typedef struct {
                               the whole K if it fits a quarter of the free
                               device memory, else a quarter of it, at most
                               8 GiB (the memory is kept for the next
-                              training: svm_cache_release) */
+                              training: svm_cache_release).  When the budget
+                              holds the whole K of a dense problem and n^2 d
+                              is at most 6e10 (n <= 61440), K is computed at
+                              once and the outer iterations run many to a
+                              launch (working sets of at most 16; not with
+                              profile or fused); the trainings of a
+                              one-vs-rest model or a cross-validation then
+                              run side by side.  Results are the same bits */
     void *stream;          /* hipStream_t; NULL: a stream of the library */
     int32_t check_every;   /* outer iterations between host polls (0: 64;
                               fewer near convergence, down to an eighth,
@@ -149,7 +156,9 @@ typedef struct {
                               needs dense X and working_set = 16, else
                               SVM_E_UNSUPPORTED.  No effect on svm_train.
                               train_ms of a problem then spans its group's
-                              run (the groups' problems overlap in time) */
+                              run (the groups' problems overlap in time).
+                              Not used where the whole K is in the cache
+                              (cache_bytes) */
     int32_t fused;         /* 1: every outer iteration as one launch, in
                               which each block merges the selection
                               candidates and solves the subproblem itself
@@ -202,7 +211,11 @@ typedef struct {
     double dual_obj;       /* f(a) of Eq. 2 */
     int64_t kernel_rows;   /* kernel rows K(x_s, X) used (computed + cached) */
     int64_t cache_hits;    /* kernel rows served by the row cache */
-    int64_t cache_fills;   /* kernel rows written to the row cache */
+    int64_t cache_fills;   /* kernel rows written to the row cache (K
+                              computed at once: rows of samples used for the
+                              first time in this training; rows served: of
+                              working sets whose samples were all used
+                              before) */
     double train_ms;       /* device time from solver start to model ready */
     /* profile = 1: row/update kernel launches that computed the rows from X */
     double row_kernel_ms;        /* summed kernel time */

@@ -417,12 +417,15 @@ svm_status svm_train_ovr(const svm_matrix* X, const int32_t* labels,
         s.get_alpha(m->alpha[(size_t)c].data());
         if (r.status != SVM_OK) worst = r.status;
     };
-    const int L = lock_group(p, f);
+    // with the whole kernel matrix at hand the classes train side by side
+    const bool res_fit = msvm::Solver::resident_fits(o, f, rc);
+    const int L = res_fit ? msvm::Solver::resident_capacity(n, p->device)
+                          : lock_group(p, f);
     for (int32_t c0 = 0; c0 < n_classes; c0 += L) {
         const int G = std::min<int>(L, n_classes - c0);
         if (G == 1) {
             msvm::launch_ovr_labels(ld.p, n, c0, yc.p, cx.stream);
-            msvm::Solver s(cx, f, yc.p, o, L > 1 ? nullptr : &rc);
+            msvm::Solver s(cx, f, yc.p, o, L > 1 && !res_fit ? nullptr : &rc);
             collect(c0, s, s.train());
             continue;
         }
@@ -430,11 +433,13 @@ svm_status svm_train_ovr(const svm_matrix* X, const int32_t* labels,
         std::vector<msvm::Solver*> gp;
         for (int j = 0; j < G; ++j) {
             msvm::launch_ovr_labels(ld.p, n, c0 + j, yc.p, cx.stream);
-            ss.emplace_back(new msvm::Solver(cx, f, yc.p, o));
+            ss.emplace_back(
+                new msvm::Solver(cx, f, yc.p, o, res_fit ? &rc : nullptr));
             gp.push_back(ss.back().get());
         }
         const std::vector<msvm::SolveResult> rr =
-            msvm::Solver::train_lockstep(gp);
+            res_fit ? msvm::Solver::train_resident(gp)
+                    : msvm::Solver::train_lockstep(gp);
         for (int j = 0; j < G; ++j) collect(c0 + j, *gp[j], rr[(size_t)j]);
     }
     msvm::build_model(*m, cx, f, coef.p, n_classes);
@@ -696,51 +701,63 @@ svm_status cv_run_many(CvData& c, const std::vector<svm_params>& ps,
     };
     const int L = lock_group(&ps[0], c.f);
     const int32_t per = k * c.n_out;  // trainings of one parameter set
-    if (L == 1) {
-        for (int g = 0; g < NG; ++g) {
-            msvm::RowCache rc;  // K rows do not depend on fold or class
-            msvm::cache_init(rc, n,
-                             msvm::one_launch_loop(opts[(size_t)g], c.f)
-                                 ? -1
-                                 : ps[(size_t)g].cache_bytes,
-                             cx);
-            for (int32_t t = 0; t < per; ++t) {
-                const int32_t fo = t / c.n_out, cl = t % c.n_out;
-                if (c.labels.p)
-                    msvm::launch_ovr_labels(c.labels.p, n, cl, c.y.p,
-                                            cx.stream);
-                msvm::Solver s(cx, c.f, c.y.p, opts[(size_t)g], &rc,
-                               c.fold.p, fo);
-                collect(g, fo, cl, s, s.train());
-            }
+    // training t of parameter set g
+    auto make = [&](int g, int32_t t, msvm::RowCache* rc) {
+        const int32_t fo = t / c.n_out, cl = t % c.n_out;
+        if (c.labels.p)
+            msvm::launch_ovr_labels(c.labels.p, n, cl, c.y.p, cx.stream);
+        return std::make_unique<msvm::Solver>(cx, c.f, c.y.p, opts[(size_t)g],
+                                              rc, c.fold.p, fo);
+    };
+    std::vector<int> later;  // parameter sets left to lockstep
+    for (int g = 0; g < NG; ++g) {
+        const msvm::SolveOptions& o = opts[(size_t)g];
+        msvm::RowCache rc;  // K rows do not depend on fold or class
+        if (L == 1 || msvm::Solver::resident_may_fit(o, c.f))
+            msvm::cache_init(
+                rc, n,
+                msvm::one_launch_loop(o, c.f) ? -1 : ps[(size_t)g].cache_bytes,
+                cx);
+        const bool res_fit = msvm::Solver::resident_fits(o, c.f, rc);
+        if (L > 1 && !res_fit) {
+            later.push_back(g);
+            continue;
         }
-    } else {
-        const int32_t T = NG * per;
-        for (int32_t t0 = 0; t0 < T; t0 += L) {
-            const int G = std::min<int>(L, T - t0);
+        // with the whole kernel matrix at hand the trainings run side by
+        // side, else one after another
+        const int W = res_fit ? msvm::Solver::resident_capacity(n, cx.device)
+                              : 1;
+        for (int32_t t0 = 0; t0 < per; t0 += W) {
             std::vector<std::unique_ptr<msvm::Solver>> ss;
             std::vector<msvm::Solver*> gp;
-            for (int j = 0; j < G; ++j) {
-                const int32_t t = t0 + j, g = t / per, r = t % per;
-                const int32_t fo = r / c.n_out, cl = r % c.n_out;
-                if (c.labels.p)
-                    msvm::launch_ovr_labels(c.labels.p, n, cl, c.y.p,
-                                            cx.stream);
-                ss.emplace_back(new msvm::Solver(cx, c.f, c.y.p,
-                                                 opts[(size_t)g], nullptr,
-                                                 c.fold.p, fo));
+            for (int32_t t = t0; t < std::min<int32_t>(per, t0 + W); ++t) {
+                ss.push_back(make(g, t, &rc));
                 gp.push_back(ss.back().get());
             }
             std::vector<msvm::SolveResult> rr;
-            if (G == 1)
-                rr.push_back(gp[0]->train());
-            else
-                rr = msvm::Solver::train_lockstep(gp);
-            for (int j = 0; j < G; ++j) {
-                const int32_t t = t0 + j, g = t / per, r = t % per;
-                collect(g, r / c.n_out, r % c.n_out, *gp[(size_t)j],
-                        rr[(size_t)j]);
-            }
+            if (res_fit) rr = msvm::Solver::train_resident(gp);
+            else rr.push_back(gp[0]->train());
+            for (size_t j = 0; j < gp.size(); ++j)
+                collect(g, (t0 + (int32_t)j) / c.n_out,
+                        (t0 + (int32_t)j) % c.n_out, *gp[j], rr[j]);
+        }
+    }
+    const int32_t T = (int32_t)later.size() * per;
+    for (int32_t t0 = 0; t0 < T; t0 += L) {
+        const int G = std::min<int>(L, T - t0);
+        std::vector<std::unique_ptr<msvm::Solver>> ss;
+        std::vector<msvm::Solver*> gp;
+        for (int32_t t = t0; t < t0 + G; ++t) {
+            ss.push_back(make(later[(size_t)(t / per)], t % per, nullptr));
+            gp.push_back(ss.back().get());
+        }
+        std::vector<msvm::SolveResult> rr;
+        if (G == 1) rr.push_back(gp[0]->train());
+        else rr = msvm::Solver::train_lockstep(gp);
+        for (int j = 0; j < G; ++j) {
+            const int32_t t = t0 + j, r = t % per;
+            collect(later[(size_t)(t / per)], r / c.n_out, r % c.n_out,
+                    *gp[(size_t)j], rr[(size_t)j]);
         }
     }
     stats.assign((size_t)NG, svm_cv_stats{});

@@ -2,6 +2,8 @@
 // the final recompute of the responses, bias, objective and the model.
 #include "solver.hpp"
 
+#include "resident.hpp"
+
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -328,6 +330,7 @@ void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx)
     HIP_TRY(hipMemsetAsync(c.owner.p, 0xFF, c.owner.bytes(), cx.stream));
     HIP_TRY(hipMemsetAsync(c.clock.p, 0, c.clock.bytes(), cx.stream));
     c.slots = slots;
+    c.full = false;
 }
 
 Solver::Solver(Context& cx, const Features& f, const float* y_dev,
@@ -429,6 +432,8 @@ Solver::Solver(Context& cx, const Features& f, const float* y_dev,
             cache_ = nullptr;  // (the row cache serves the two-launch loop)
         }
     }
+
+    resident_ = cache_ && resident_fits(o, f, *cache_);
 
     F_.alloc((size_t)n_);
     alpha_.alloc((size_t)N_);
@@ -927,8 +932,216 @@ bool Solver::run_loop_fused(SolveResult& r)
     return w.done == 1;
 }
 
+// The kernel matrix is computed whole when that takes at most about a
+// millisecond (n^2 d / 2 products on the matrix cores; a solve touches some
+// 10 to 90 % of its rows, and the loop that needs no row of X is 2 to 3 times
+// as fast), and the blocks of one problem fit the chip.
+constexpr double kGramWork = 6e10;
+
+// Blocks of a problem: as few as hold its rows (the exchange between blocks
+// costs about 1.5 us an iteration, whatever their number up to 4).
+static int64_t resident_blocks(int64_t n)
+{
+    return (n + kResRows - 1) / kResRows;
+}
+
+bool Solver::resident_may_fit(const SolveOptions& o, const Features& f)
+{
+    return !f.csr && o.q <= 16 && !o.profile && !o.fused && f.n >= 2 &&
+           resident_blocks(f.n) <= kResBlocks &&
+           (double)f.n * (double)f.n * (double)f.ldp <= kGramWork &&
+           64 * f.ldp * 4 < ((int64_t)1 << 31);
+}
+
+bool Solver::resident_fits(const SolveOptions& o, const Features& f,
+                           const RowCache& c)
+{
+    return resident_may_fit(o, f) && c.slots >= f.n;
+}
+
+int Solver::resident_capacity(int64_t n, int device)
+{
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount,
+                                  device));
+    return std::max(1, (int)(cus / resident_blocks(n)));
+}
+
+void Solver::fill_result(const WorkingSet& w, SolveResult& r) const
+{
+    r.iters = w.iter;
+    r.gap = w.gap;
+    r.m = w.m;
+    r.M = w.M;
+    r.kernel_rows = w.rows;
+    r.status = w.done == 2 ? SVM_W_MAX_ITER : SVM_OK;
+}
+
+// The cache as the two-launch loop takes it: empty.
+void Solver::leave_resident()
+{
+    hipStream_t s = cx_.stream;
+    cache_->full = false;
+    HIP_TRY(hipMemsetAsync(cache_->slot_of.p, 0xFF, cache_->slot_of.bytes(), s));
+    HIP_TRY(hipMemsetAsync(cache_->owner.p, 0xFF, cache_->owner.bytes(), s));
+    HIP_TRY(hipMemsetAsync(cache_->clock.p, 0, cache_->clock.bytes(), s));
+    resident_ = false;
+}
+
+bool Solver::run_resident(const std::vector<Solver*>& g,
+                          std::vector<SolveResult>& r,
+                          std::vector<char>& conv)
+{
+    const int G = (int)g.size();
+    Solver& s0 = *g[0];
+    Context& cx = s0.cx_;
+    hipStream_t st = cx.stream;
+    const Features& f = s0.f_;
+    const int64_t n = s0.n_;
+    RowCache& rc = *s0.cache_;
+    if (!rc.full) {
+        launch_gram(f.x(), f.sq.p, n, f.ldp, s0.kf_, rc.rows.p, rc.ldc, st);
+        rc.full = true;
+    }
+    const int R = (int)resident_blocks(n);
+    const size_t xw = resident_xch_words(R, s0.half_);
+    DevBuf<uint64_t> xch(R > 1 ? xw * G : 1);
+    DevBuf<uint32_t> hs((size_t)4 * G);  // two launches in flight
+    DevBuf<ResidentProblem> pd((size_t)G);
+    HostBuf<ResidentProblem> ph((size_t)G);
+    if (R > 1) HIP_TRY(hipMemsetAsync(xch.p, 0, xch.bytes(), st));
+    for (Solver* s : g)
+        if (s->seen_.count < (size_t)n) {
+            s->seen_.alloc((size_t)n);
+            HIP_TRY(hipMemsetAsync(s->seen_.p, 0xFF, s->seen_.bytes(), st));
+        }
+    for (int p = 0; p < G; ++p) {
+        Solver& s = *g[p];
+        ResidentProblem q{};
+        q.K = rc.rows.p;
+        q.F = s.F_.p;
+        q.alpha = s.alpha_.p;
+        q.st = s.st_.p;
+        q.z = s.y_.p;
+        q.ws = s.ws_.p;
+        q.seen = s.seen_.p;
+        q.xch = xch.p + xw * (R > 1 ? p : 0);
+        q.C = s.o_.C;
+        q.eps = s.o_.eps;
+        q.tol = s.o_.tol;
+        q.inner_ratio = s.o_.inner_ratio;
+        q.max_iter = s.o_.max_iter;
+        q.max_inner = s.o_.max_inner;
+        ph.p[p] = q;
+    }
+    HIP_TRY(hipMemcpyAsync(pd.p, ph.p, (size_t)G * sizeof(ResidentProblem),
+                           hipMemcpyHostToDevice, st));
+    ResidentArgs a{};
+    a.p = pd.p;
+    a.n = n;
+    a.ldc = rc.ldc;
+    a.R = R;
+    a.half = s0.half_;
+    // (a launch reads and writes the whole state once: 4 polls' worth)
+    a.iters = 4 * s0.o_.check_every;
+    a.wait = 2000000;  // 20 ms
+    if (const char* e = getenv("SVM_RESIDENT_WAIT"))  // developer override
+        a.wait = (uint64_t)std::max(0, atoi(e));
+    const bool svr = s0.o_.type == SVM_EPS_SVR;
+
+    HostBuf<WorkingSet> hw((size_t)2 * G);
+    struct Events {
+        hipEvent_t e[2] = {nullptr, nullptr};
+        ~Events()
+        {
+            for (auto& x : e)
+                if (x) (void)hipEventDestroy(x);
+        }
+    } ev;
+    for (auto& x : ev.e)
+        HIP_TRY(hipEventCreateWithFlags(&x, hipEventDisableTiming));
+    auto enqueue = [&](int slot) {
+        a.hs = hs.p + (size_t)2 * G * slot;
+        if (R > 1)
+            HIP_TRY(hipMemsetAsync(a.hs, 0, (size_t)2 * G * sizeof(uint32_t),
+                                   st));
+        launch_resident(a, G, svr, st);
+        for (int p = 0; p < G; ++p)
+            HIP_TRY(hipMemcpyAsync(&hw.p[(size_t)slot * G + p], g[p]->ws_.p,
+                                   sizeof(WorkingSet), hipMemcpyDeviceToHost,
+                                   st));
+        HIP_TRY(hipEventRecord(ev.e[slot], st));
+    };
+    bool ok = true;
+    try {
+        enqueue(0);
+        enqueue(1);
+        int cur = 0;
+        for (;;) {
+            HIP_TRY(hipEventSynchronize(ev.e[cur]));
+            bool run = false;
+            for (int p = 0; p < G; ++p) {
+                const WorkingSet& w = hw.p[(size_t)cur * G + p];
+                run |= !w.done;
+                if (w.pad0) ok = false;
+            }
+            if (!run || !ok) break;
+            enqueue(cur);
+            cur ^= 1;
+        }
+    } catch (...) {
+        cx.sync();
+        throw;
+    }
+    cx.sync();
+    for (int p = 0; p < G; ++p) {
+        WorkingSet w;
+        g[p]->read_ws(w);
+        g[p]->fill_result(w, r[(size_t)p]);
+        conv[(size_t)p] = w.done == 1;
+        if (!ok) launch_fill_i32(&g[p]->ws_.p->pad0, 0, 1, st);
+    }
+    return ok;
+}
+
+std::vector<SolveResult> Solver::train_resident(const std::vector<Solver*>& g)
+{
+    const size_t G = g.size();
+    std::vector<SolveResult> r(G);
+    if (G == 0) return r;
+    Solver& s0 = *g[0];
+    for (Solver* s : g)
+        if (!s->resident_ || &s->f_ != &s0.f_ || &s->cx_ != &s0.cx_ ||
+            s->cache_ != s0.cache_ || s->o_.type != s0.o_.type ||
+            s->half_ != s0.half_)
+            throw Error{SVM_E_INTERNAL, "solvers cannot run side by side"};
+    std::vector<hipEvent_t> t0(G);
+    for (size_t p = 0; p < G; ++p) t0[p] = g[p]->start(false);
+    std::vector<char> conv(G, 0);
+    if (!run_resident(g, r, conv)) {
+        s0.leave_resident();
+        for (size_t p = 0; p < G; ++p) {
+            g[p]->resident_ = false;
+            g[p]->launch_keys();
+            conv[p] = g[p]->run_loop(r[p]);
+        }
+    }
+    for (size_t p = 0; p < G; ++p) g[p]->finish(r[p], conv[p], t0[p]);
+    return r;
+}
+
 bool Solver::loop(SolveResult& r)
 {
+    if (resident_) {
+        std::vector<SolveResult> rr(1, r);
+        std::vector<char> conv(1, 0);
+        const bool ok = run_resident({this}, rr, conv);
+        r = rr[0];
+        if (ok) return conv[0] != 0;
+        leave_resident();
+        launch_keys();
+        return run_loop(r);
+    }
     if (!fused_) return run_loop(r);  // (candidates from launch_keys)
     launch_keys_fused();
     return run_loop_fused(r);
@@ -985,7 +1198,7 @@ void Solver::recompute_responses()
 SolveResult Solver::train()
 {
     SolveResult r;
-    hipEvent_t t0 = start(!fused_);
+    hipEvent_t t0 = start(!fused_ && !resident_);
     bool conv;
     {
         Range rg("svm solve loop");

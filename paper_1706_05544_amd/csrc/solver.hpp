@@ -114,6 +114,9 @@ struct RowCache {
     CacheRows rows;
     DevBuf<int32_t> slot_of, owner;
     DevBuf<int64_t> clock;
+    // every row computed, row s in slot s (the solves that run as k_resident;
+    // slot_of and owner are not used then)
+    bool full = false;
 };
 
 // Sizes and clears the cache for n samples.  bytes: 0 = default (the full
@@ -231,6 +234,19 @@ public:
     // dense features and no row cache; at most lock_capacity() of them.
     static std::vector<SolveResult> train_lockstep(
         const std::vector<Solver*>& group);
+    // Whether a solve of these options on these features holds the whole
+    // kernel matrix in the cache and runs as k_resident.
+    static bool resident_fits(const SolveOptions& o, const Features& f,
+                              const RowCache& c);
+    // ... if the cache holds the whole matrix
+    static bool resident_may_fit(const SolveOptions& o, const Features& f);
+    // Training of several solvers for which resident_fits(), side by side:
+    // each has compute units of its own and the same result as alone.  They
+    // share the features, the stream, the type and the kernel matrix.
+    static std::vector<SolveResult> train_resident(
+        const std::vector<Solver*>& group);
+    // Problems one train_resident call runs side by side.
+    static int resident_capacity(int64_t n, int device);
     // Problems one lockstep pass can carry for these features (their
     // working-set rows share the row kernel's LDS): 1 .. kLockMax.
     static int lock_capacity(const Features& f, int32_t type);
@@ -277,6 +293,14 @@ private:
                       hipEvent_t e1 = nullptr);
     void launch_select_only();
     bool run_loop(SolveResult& r);
+    // the loops of the group's solvers as k_resident launches (conv[p]:
+    // converged); false when a launch could not start (the states are then
+    // whole, and the two-launch loop takes over)
+    static bool run_resident(const std::vector<Solver*>& g,
+                             std::vector<SolveResult>& r,
+                             std::vector<char>& conv);
+    void leave_resident();
+    void fill_result(const WorkingSet& w, SolveResult& r) const;
     // one launch per outer iteration: initial records, the loop
     void launch_keys_fused();
     bool run_loop_fused(SolveResult& r);
@@ -300,6 +324,8 @@ private:
     // per row wave, tiles of the record-writing k_rows launch on that grid;
     // the second responses buffer, the double-buffered records, the ticket
     bool fused_ = false;
+    bool resident_ = false;  // the loop is k_resident
+    DevBuf<int32_t> seen_;   // its samples used so far
     int nbi_ = 0, tilesi_ = 0, tilesk_ = 0;
     DevBuf<double> F2_, irk_;
     DevBuf<int32_t> iri_;

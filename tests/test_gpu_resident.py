@@ -1,0 +1,108 @@
+"""The loop that runs many outer iterations to a launch (k_resident) on the GPU.
+
+It takes dense problems whose whole kernel matrix the row cache holds, and
+promises the bits of the two-launch loop: working sets, alpha, bias,
+objective and iteration counts.  So the bar is equality with the same
+training without the row cache, which the other tests tie to the oracle.
+Sizes sit at its edges: two rows a thread, 1920 rows a block, one to several
+blocks that exchange their candidates, the smallest problems, working sets
+of 2 to 16, ties of every key (alpha = 0) past the candidate list, eps-SVR
+with both copies of a sample in a working set.
+"""
+import numpy as np
+import pytest
+
+from paper_1706_05544_amd import native as nv
+from paper_1706_05544_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+SAME = ("iters", "b", "dual_obj", "gap", "kernel_rows", "status", "n_bounded")
+
+
+def _train(w, **kw):
+    k = dict(type=w.type, C=w.C, epsilon=w.eps, gamma=w.gamma, tol=w.tol)
+    k.update(kw)
+    m = nv.svm_train(w.X, w.y, **k)
+    return m.info(), nv.svm_model_get(m, 0, with_alpha=True)[2]
+
+
+def _same(w, **kw):
+    i0, a0 = _train(w, cache_bytes=-1, **kw)
+    i1, a1 = _train(w, **kw)
+    np.testing.assert_array_equal(a1, a0)
+    for k in SAME:
+        assert i1[k] == i0[k], k
+    # served from the cache: the loop under test ran
+    assert i1["cache_hits"] + i1["cache_fills"] > 0
+    return i1
+
+
+@pytest.mark.parametrize("name,n,kw", [
+    ("C1", 2, {}), ("C1", 3, {}), ("C1", 31, {}), ("C2", 29, {}),
+    ("C1", 600, {}), ("C1", 1919, {}), ("C1", 1920, {}), ("C1", 1921, {}),
+    ("C2", 1921, {}), ("C1", 3841, {}), ("C2", 3000, {}),
+    ("C3", 12345, {}),
+    ("C1", 777, dict(working_set=2)), ("C2", 2500, dict(working_set=6)),
+    ("C1", 2100, dict(working_set=14)),
+    ("C1", 1000, dict(kernel=1, coef0=1.0)), ("C1", 1000, dict(kernel=3)),
+    ("C2", 2001, dict(kernel=0, max_iter=300)),
+    ("C1", 1500, dict(max_iter=7)), ("C1", 2000, dict(check_every=3)),
+    ("C1", 900, dict(max_inner=1)), ("C1", 1500, dict(scale=1)),
+])
+def test_same_bits_as_the_two_launch_loop(name, n, kw):
+    _same(workloads.make(name, n=n, n_test=4), **kw)
+
+
+def test_duplicate_rows():
+    # equal rows: zero curvature, equal keys all along
+    w = workloads.make("C2", n=2200, n_test=4)
+    w.X[1100:] = w.X[:1100]
+    _same(w, max_iter=400)
+
+
+def test_launch_called_off():
+    # no time to wait for a problem's blocks: launches are called off and the
+    # two-launch loop takes over from the state they left
+    import os
+    w = workloads.make("C2", n=4100, n_test=4)
+    i0, a0 = _train(w, cache_bytes=-1)
+    os.environ["SVM_RESIDENT_WAIT"] = "0"
+    try:
+        for _ in range(3):
+            i1, a1 = _train(w)
+            np.testing.assert_array_equal(a1, a0)
+            assert i1["iters"] == i0["iters"] and i1["b"] == i0["b"]
+    finally:
+        del os.environ["SVM_RESIDENT_WAIT"]
+
+
+@pytest.mark.parametrize("name,n,k,lockstep", [
+    ("C1", 501, 3, 0), ("C2", 700, 4, 4), ("C1", 4000, 5, 2)])
+def test_cross_validation_side_by_side(name, n, k, lockstep):
+    w = workloads.make(name, n=n, n_test=4)
+    kw = dict(k=k, type=w.type, C=w.C, epsilon=w.eps, gamma=w.gamma,
+              tol=w.tol, lockstep=lockstep)
+    D0, s0 = nv.svm_cross_validate(w.X, w.y, cache_bytes=-1, **kw)
+    D1, s1 = nv.svm_cross_validate(w.X, w.y, **kw)
+    np.testing.assert_array_equal(D1, D0)
+    for key in ("iters", "kernel_rows", "accuracy", "mse", "status"):
+        assert s1[key] == s0[key], key
+
+
+def test_ovr_and_tuning_side_by_side():
+    w = workloads.make("C4", n=2003, n_test=50)
+    kw = dict(C=w.C, gamma=w.gamma, tol=w.tol)
+    m0 = nv.svm_train_ovr(w.X, w.y, w.n_classes, cache_bytes=-1, **kw)
+    m1 = nv.svm_train_ovr(w.X, w.y, w.n_classes, **kw)
+    for c in range(w.n_classes):
+        np.testing.assert_array_equal(
+            nv.svm_model_get(m1, c, with_alpha=True)[2],
+            nv.svm_model_get(m0, c, with_alpha=True)[2])
+    w = workloads.c1(n=900, n_test=4)
+    kw = dict(k=3, C=np.array([0.1, 1.0, 10.0]),
+              gamma=np.array([0.05, 0.05, 0.2]), tol=w.tol)
+    e0, b0 = nv.svm_tune(w.X, w.y, cache_bytes=-1, **kw)
+    e1, b1 = nv.svm_tune(w.X, w.y, **kw)
+    np.testing.assert_array_equal(e1, e0)
+    assert b0 == b1
