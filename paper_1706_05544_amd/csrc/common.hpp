@@ -68,13 +68,22 @@ struct WorkingSet {
     // kernel-row cache
     int32_t path;             // PATH_* of the current iteration
     int32_t pad2;
-    int32_t cslot[kMaxQ];     // cache slot of each working-set slot (cached:
-                              // source; insert: destination or -1)
+    int32_t cslot[kMaxQ];     // cached: cache slot of each working-set slot;
+                              // insert: destination of each computed column
+                              // or -1
+    // the columns that the row kernel computes: the working-set slots, but
+    // (insert, dense) a slot whose sample is cached has its row read from
+    // cache slot hsrc (else -1) and its column computes a row that later
+    // working sets are likely to need
+    int32_t hsrc[kMaxQ];
+    int32_t colS[kMaxQ];      // sample of each column, or -1
+    float colq[kMaxQ];        // its squared norm
     int64_t cache_served;     // kernel rows read from the cache
     int64_t cache_filled;     // kernel rows written to the cache
     uint8_t path_log[kPathLog];  // path of iteration t at [t % kPathLog]
     uint8_t fill_log[kPathLog];  // rows written to the cache by iteration t
     uint8_t ns_log[kPathLog];    // distinct samples of iteration t
+    uint8_t hit_log[kPathLog];   // insert: rows of them read from the cache
 };
 
 // Final reductions of a state (bias and objective).
@@ -136,7 +145,7 @@ struct RowArgs {
     const int32_t* xsc_cols;
     const float* xsc;
     int32_t csr_cols;
-    double* cand_key;     // [blocks][2][kBlockTop]: up scores v, low -v
+    double* cand_key;     // [records][2][kBlockTop]: up scores v, low -v
     int32_t* cand_idx;
     float* rows_out;      // nS x n (tests)
     float* cache;         // kernel-row cache rows (stride ldc), or nullptr
@@ -146,6 +155,7 @@ struct RowArgs {
     KernelFn kf;
     int32_t half;
     int32_t tiles;        // 16-row tiles per wave
+    int32_t sub;          // candidate records per block: 1, or 4 (a wave each)
     int32_t mode;
     int32_t nS_override;  // >= 0: use this many slots (tests), else ws->nS
 };
@@ -153,7 +163,7 @@ struct RowArgs {
 struct SelArgs {
     const double* cand_key;
     const int32_t* cand_idx;
-    int32_t nb, half;     // nb: candidate records (one per k_rows block)
+    int32_t nb, half;     // nb: candidate records (sub per k_rows block)
     WorkingSet* ws;
     double* alpha;
     uint8_t* st;
@@ -176,7 +186,8 @@ struct SelArgs {
     int32_t max_inner;
     int64_t max_iter;
     int32_t mode;
-    int32_t group_rows;   // rows behind one candidate record (a k_rows block)
+    int32_t group_rows;   // most rows behind one candidate record
+    int32_t sub;          // records of a k_rows block: 1 or 4 (lockstep: 1)
     int32_t slice;        // features per LDS slice of the working-set rows
     // kernel-row cache (cache_slots == 0: none)
     const float* cache;   // cache_slots rows of ldc floats

@@ -265,11 +265,11 @@ __device__ bool resident_start(uint32_t* hs, int R, uint64_t wait)
 // Waves 1 .. 15 hold the rows, two consecutive ones a thread, dealt evenly to
 // the waves (four rows a thread took 3.1 us for the update and the keys of
 // an iteration against 1.2: the instructions of the four waves of a SIMD
-// follow one another); wave 0 builds the working set and solves.  While wave 0 builds,
-// other waves fetch what the subproblem needs (K_BB, alpha) by candidate, so
-// that its memory latency is not on the chain; the 16 kernel rows of the
-// update are requested when the working set is known and arrive while wave
-// 0 solves.
+// follow one another); wave 0 builds the working set and solves.  While wave
+// 0 builds, other waves fetch what the subproblem needs (K_BB, alpha) by
+// candidate, so that its memory latency is not on the chain; the 16 kernel
+// rows of the update are requested when the working set is known and arrive
+// while wave 0 solves.
 template <bool SVR>
 __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
 {
@@ -551,8 +551,9 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
                         kb == -INFINITY ? 0 : (SVR && ib >= n ? ib - n : ib);
                     kbb[ca][cb] = K[(int64_t)sa * ldc + sb];
                 } else if (wave == 12 && lane < 16) {
-                    // their alpha (written by whichever block holds the variable, so
-                    // read past the caches), labels and first use
+                    // their alpha (written by whichever block holds the
+                    // variable, so read past the caches), labels and first
+                    // use
                     double key;
                     int32_t idx;
                     cand(lane, key, idx);
@@ -776,7 +777,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
             // 4 r + 3; a step reads its pair's
             {
                 const float kpp = kbb[cp][cp];
-                const int4 cc = *reinterpret_cast<const int4*>(shCand + 4 * prow);
+                const int4 cc =
+                    *reinterpret_cast<const int4*>(shCand + 4 * prow);
                 const int cx[4] = {cc.x, cc.y, cc.z, cc.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {

@@ -92,7 +92,9 @@ size_t rows_lds_bytes(int nblk_cols, int64_t ldp, int tiles, bool svr,
 // 16c + 4g .. +3 of chunk c), which is the library-wide chunk order, so every
 // K value matches the other kernels bitwise.
 template <bool SVR, int NBLK, int MODE, bool CSR>
-__global__ __launch_bounds__(kRowThreads) void k_rows(RowArgs a)
+__global__ __launch_bounds__(kRowThreads)
+__attribute__((amdgpu_waves_per_eu(NBLK == 1 && !CSR ? 4 : 1)))
+void k_rows(RowArgs a)
 {
     constexpr bool UPD = (MODE & RU_UPDATE) != 0;
     constexpr bool ROWS = (MODE & RU_ROWS) != 0;
@@ -248,11 +250,14 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(RowArgs a)
         // (dense, hot mode) the cache slot of this lane's working-set slots,
         // requested with the path and waited for with it: issued inside the
         // cached branch, it would be a second round trip after the path's
-        int32_t cs_in[NBLK];
+        // (insert path: and the cache slot of a slot whose row is read
+        // instead of computed, hs_in)
+        int32_t cs_in[NBLK], hs_in[NBLK];
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) {
             cs_in[b] = (HOT && !CSR) ? ws->cslot[b * 16 + nl] : -1;
-            if (HOT && !CSR) asm volatile("" ::"v"(cs_in[b]));
+            hs_in[b] = (HOT && !CSR) ? ws->hsrc[b * 16 + nl] : -1;
+            if (HOT && !CSR) asm volatile("" ::"v"(cs_in[b]), "v"(hs_in[b]));
         }
 
         // F_i += sum_s cf_s K(x_i, x_s) for the 16 rows of tile ti, given
@@ -696,11 +701,16 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(RowArgs a)
             float sq0 = 0.0f;
             int32_t smp0 = -1, cs0 = -1;
             if (tid < NBLK * 16) {
-                const float q = ws->sS[tid];
-                const int32_t i = ws->S[tid], c = ws->cslot[tid];
-                sq0 = tid < nS ? q : 0.0f;
-                smp0 = tid < nS ? i : -1;
-                cs0 = (HOT && tid < nS) ? c : -1;
+                if (HOT) {  // the columns computed (see WorkingSet)
+                    sq0 = ws->colq[tid];
+                    smp0 = ws->colS[tid];
+                    cs0 = ws->cslot[tid];
+                } else {
+                    const float q = ws->sS[tid];
+                    const int32_t i = ws->S[tid];
+                    sq0 = tid < nS ? q : 0.0f;
+                    smp0 = tid < nS ? i : -1;
+                }
             }
             float4 xv[kXsEarly];
 #pragma unroll
@@ -745,6 +755,18 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(RowArgs a)
             // missing from the cache also go to their new cache slots.
             {
                 const bool INS = HOT && path == PATH_INSERT;
+                // the rows of cached slots, one tile ahead (lanes whose slot
+                // is computed read a valid address of the cache)
+                float4 hv[NBLK];
+                auto hfetch = [&](int t) {
+#pragma unroll
+                    for (int b = 0; b < NBLK; ++b)
+                        hv[b] = ld4(a.cache +
+                                    (int64_t)max(hs_in[b], 0) * a.ldc +
+                                    (nw > 0 ? rw0 : 0) +
+                                    16 * min(t, max(Tw - 1, 0)) + 4 * g);
+                };
+                if (INS) hfetch(0);
                 floatx4 acc[NBLK];
                 int pti = 0, psl = 0;  // slab being processed
                 for (int s0 = 0; s0 < Tw * nslab; s0 += kRing) {
@@ -821,7 +843,15 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(RowArgs a)
                                         a.cache + (int64_t)csb * a.ldc + rw0 +
                                         lr) = make_float4(kv[b][0], kv[b][1],
                                                           kv[b][2], kv[b][3]);
+                                if (INS && hs_in[b] >= 0) {
+                                    // a slot whose row is cached takes that
+                                    kv[b][0] = hv[b].x;
+                                    kv[b][1] = hv[b].y;
+                                    kv[b][2] = hv[b].z;
+                                    kv[b][3] = hv[b].w;
+                                }
                             }
+                            if (INS) hfetch(pti + 1);
                             finish_tile(pti, kv);
                         }
                         if (++psl == nslab) {
@@ -860,10 +890,16 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(RowArgs a)
     }
 
     if (!CAND) return;
-    // The best two of each side over the block's rows: every wave's best
+    // The best two of each side over the rows of each wave (a.sub = 4, few
+    // blocks of many rows), or over the block's rows: every wave's best
     // two go to the block table, then wave 0 takes the best two of those.
     // A variable outside the global top q/2 never needs more (k_select
     // rescans a row group whose two candidates were both taken).
+    if (a.sub == 4) {  // uniform: a record of each wave's rows
+        const size_t o = ((size_t)blockIdx.x * 4 + wave) * 2 * kBlockTop;
+        wave_top2_pair(up, lo, a.cand_key + o, a.cand_idx + o);
+        return;
+    }
     wave_top2_pair(up, lo, brk + 4 * wave, bri + 4 * wave);
     __syncthreads();
     if (wave == 0) {

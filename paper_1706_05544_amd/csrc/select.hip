@@ -45,6 +45,10 @@ __device__ __forceinline__ void var_scores(const SelArgs& a, int64_t t,
     lo = (s & ST_LOW) ? -v : -INFINITY;
 }
 
+// entries per side ranked past the working set for the row cache
+constexpr int kSpec = 24;
+constexpr int64_t kSpecX = (int64_t)1 << 24;  // floats of X from which on
+
 // Best (key, lane) of each side over a 16-lane row (NBLK = 1) or the wave,
 // both sides interleaved; results are wave-uniform.  Ties go to the lowest
 // lane.
@@ -130,7 +134,7 @@ __device__ __forceinline__ int flag_exclusive_scan(int* v, int64_t L,
     return tot;
 }
 
-template <bool SVR, int NBLK>
+template <bool SVR, int NBLK, bool CSR>
 __device__ __forceinline__ void select_body(const SelArgs& a)
 {
     WorkingSet* ws = a.ws;
@@ -162,6 +166,10 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     __shared__ float KSS[QS][QS + 1];
     __shared__ double shDc[kMaxQ];
     __shared__ int32_t shNB, shNS, shGo, shDone;
+    // the columns that the row kernel computes (see WorkingSet)
+    __shared__ int32_t shCol[kMaxQ], shCs[kMaxQ], shHs[kMaxQ];
+    __shared__ int32_t shPath, shFill, shHit;
+    __shared__ int64_t shClk;
     __shared__ int32_t shNoList;       // CSR: a slot's row is longer than LM
     __shared__ int32_t shLen[kMaxQ];   // CSR: nonzeros of each slot's row
 
@@ -173,6 +181,14 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     const int64_t n = a.n, ldp = a.ldp;
     const bool given = (a.mode & SS_GIVEN_B) != 0;
     if (given && done0) return;
+    // Rows that later working sets are likely to need (the variables next in
+    // the order of the keys) are computed in the columns of samples that are
+    // cached already, where a launch streams X anyway: the lists are ranked
+    // kSpec entries further for them.
+    const bool spec = NBLK == 1 && a.cache_slots > 0 && !CSR && !given &&
+                      (a.mode & SS_SOLVE) && a.slice >= ((ldp + 15) & ~15) &&
+                      a.nb >= 256 && n * ldp >= kSpecX;
+    const int want = spec ? min(half + kSpec, kMaxHalf) : half;
     // (1) the candidate records of the row groups (best two up keys, best
     // two low keys, their variables): thread t loads records t, t +
     // kSelThreads, ... with 16-byte loads, issued before anything else
@@ -270,7 +286,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
                 int c = 0;
 #pragma unroll 16
                 for (int j = 0; j < NW * 4; ++j) c += rmax[side][j] >= x;
-                double th = (c >= half && x != -INFINITY) ? x : -INFINITY;
+                double th = (c >= want && x != -INFINITY) ? x : -INFINITY;
                 th = row_max_f64(th);
                 th = fmax(fmax(rl_f64(th, 0), rl_f64(th, 16)),
                           fmax(rl_f64(th, 32), rl_f64(th, 48)));
@@ -308,7 +324,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         if (!overflow) {
             // (4) rank the survivors: side 0 on threads [0,512), side 1
             // on the rest
-            top_half(svk, svi, M0, M1, half, upk, upi, lok, loi, nsv,
+            top_half(svk, svi, M0, M1, want, upk, upi, lok, loi, nsv,
                      tid);
         } else {
             // (4') too many ties at the bound (e.g. alpha = 0): exact
@@ -334,18 +350,32 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         // of 32 rows; it has at most grows rows.
         const uint32_t grows = (uint32_t)a.group_rows;
         int32_t wgrp = -1;  // wave 0: the group of this lane's winner
-        const int64_t TU = (n + 31) >> 5, NB = a.nb;
-        // group of a row: floor(((row / 32 + 1) NB - 1) / TU), through an
+        // (sub = 4: group 4 b + w holds the 16-row tiles [w T / 4, (w + 1)
+        // T / 4) of the T of block b)
+        const int32_t sub = a.sub;
+        const int64_t TU = (n + 31) >> 5, NB = sub == 4 ? a.nb >> 2 : a.nb;
+        auto block_start = [&](int64_t b) -> int64_t {
+            return 32 * (b * TU / NB);
+        };
+        auto block_tiles = [&](int64_t b) -> int32_t {
+            return (int32_t)((min(block_start(b + 1), n) - block_start(b) +
+                              15) >> 4);
+        };
+        // block of a row: floor(((row / 32 + 1) NB - 1) / TU), through an
         // fp64 quotient corrected to the exact integer
         auto group_of = [&](int64_t row) -> int32_t {
             const int64_t x = ((row >> 5) + 1) * NB - 1;
             int64_t g = (int64_t)((double)x / (double)TU);
             if (g * TU > x) --g;
             else if ((g + 1) * TU <= x) ++g;
-            return (int32_t)g;
+            if (sub != 4) return (int32_t)g;
+            const int32_t t = (int32_t)((row - block_start(g)) >> 4);
+            return 4 * (int32_t)g + (4 * t + 3) / block_tiles(g);
         };
         auto group_start = [&](int64_t b) -> int64_t {
-            return 32 * (b * TU / NB);
+            if (sub != 4) return block_start(b);
+            const int64_t w = b & 3;
+            return block_start(b >> 2) + 16 * (w * block_tiles(b >> 2) / 4);
         };
         if (wave == 0) {
             // lanes [0, 32): the up winners, [32, 64): the low winners
@@ -481,7 +511,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // c: up winner c for c < half, else low winner c - half) while wave 0
     // builds the working set, so that the staging of the working-set rows
     // starts from them
-    const bool pfr = !given && a.rp && (a.mode & SS_SOLVE);  // uniform
+    const bool pfr = !given && CSR && (a.mode & SS_SOLVE);  // uniform
     if (pfr && wave == 1 && lane < 2 * half) {
         const int c = lane;
         const double key = c < half ? upk[c] : lok[c - half];
@@ -492,8 +522,33 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         shRpC[c][0] = r0;
         shRpC[c][1] = r1;
     }
+    // Kernel-row cache: wave 1 looks up the cache slots of the winners
+    // (lane c: candidate c as above), and with speculation those of the
+    // entries past them (lanes 16 .. 63), while wave 0 builds the working set
+    auto spec_sample = [&]() -> int32_t {
+        // (the two sides in turn, best first)
+        const int e = half + ((lane - 16) >> 1);
+        const bool lo = (lane & 1) != 0;
+        const bool ok = lane >= 16 && e < want &&
+                        (lo ? lok[e] : upk[e]) != -INFINITY;
+        return ok ? (int32_t)sample_of(SVR, lo ? loi[e] : upi[e], n) : -1;
+    };
+    int32_t hcand = -2;
+    if (use_cache) {
+        int32_t smp = -1;
+        if (lane < 2 * half) {
+            const bool u = lane < half;
+            const int c = u ? lane : lane - half;
+            if ((u ? upk[c] : lok[c]) != -INFINITY)
+                smp = (int32_t)sample_of(SVR, u ? upi[c] : loi[c], n);
+        } else if (spec) {
+            smp = spec_sample();
+        }
+        hcand = a.slot_of[max(smp, 0)];
+        if (smp < 0) hcand = -2;
+    }
     // candidate c: up winner c (c < half) or low winner c - half
-    pf = !given && !a.rp && (a.mode & SS_SOLVE) && 2 * half * pq4 <= 4 * PT;
+    pf = !given && !CSR && (a.mode & SS_SOLVE) && 2 * half * pq4 <= 4 * PT;
     if (pf && wave != 0) {
         const int pwst = a.slice + 4;
         float4 xv[4];
@@ -717,10 +772,96 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     uint32_t st_b = SVR ? 0u : (uint32_t)a.st[t_l];
 
     uint64_t t_stage = 0;
-    // Kernel-row cache (wave 1): the slot of each working-set sample,
-    // looked up while the working-set rows load.
+    // Kernel-row cache (wave 1): the slot of each working-set sample, from
+    // that of a candidate of it; lanes from 16 on keep those of the entries
+    // past the lists' heads (speculation, q <= 16).
     int32_t hslot = -1;
-    if (use_cache && lane < nS) hslot = a.slot_of[shS[lane]];
+    if (use_cache) {
+        hslot = __shfl(hcand, lane < nS ? shSlotCand[lane] : lane);
+        if (lane >= nS && (!spec || lane < 16)) hslot = -2;
+    }
+    // Its path: a working set whose samples are all cached is served from
+    // the cache; otherwise the missing rows are computed and go to it.  Rows
+    // stop going to a cache that serves almost nothing (a working set whose
+    // samples rarely all recur): the fills cost HBM writes and the two paths
+    // give the same bits.  A cache with a slot for every sample never
+    // evicts, so it keeps filling: every working set whose samples have all
+    // been used before is then served.
+    if (wave == 1) {
+        int path = PATH_STREAM, nfill = 0, nhit = 0;
+        int32_t cslot = -1, hsrc = -1;
+        int32_t col = lane < nS ? shS[lane] : -1;
+        if (use_cache) {
+            const bool miss = lane < nS && hslot < 0;
+            const bool fill = a.cache_slots >= a.n || iter0 < 512 ||
+                              c_served * 8 >= c_filled;
+            if (__ballot(miss) == 0) {
+                path = PATH_CACHED;
+                cslot = lane < nS ? hslot : -1;
+            } else if (fill) {
+                // each missing sample gets a cache slot (FIFO, never a slot
+                // this working set reads)
+                path = PATH_INSERT;
+                bool fills = miss;
+                if (spec) {
+                    // the columns of cached samples and past nS, in order,
+                    // take the entries that are neither in the working set
+                    // nor cached (no sample twice)
+                    if (lane < nS && !miss) hsrc = hslot;
+                    const bool freec = lane < 16 && !miss;
+                    if (freec) col = -1;
+                    const int32_t cs = spec_sample();
+                    bool cv = cs >= 0 && hslot < 0;
+#pragma unroll 1
+                    for (int j = 0; j < nS; ++j) cv &= shS[j] != cs;
+                    const unsigned long long fm = __ballot(freec);
+                    const int r = lanes_below(fm), nf = __popcll(fm);
+                    unsigned long long q = __ballot(cv);
+#pragma unroll 1
+                    for (int j = 0; j < nf && q; ++j) {
+                        const int32_t v = rl_i32(cs, __builtin_ctzll(q));
+                        q &= ~__ballot(cs == v);
+                        if (freec && r == j) {
+                            col = v;
+                            fills = true;
+                        }
+                    }
+                    nhit = __popcll(__ballot(hsrc >= 0));
+                }
+                const unsigned long long fillm = __ballot(fills);
+                nfill = __popcll(fillm);
+                int64_t clk = clk0;
+                if (a.cache_slots >= a.n) {
+                    // never wraps: a sample takes a slot once
+                    if (fills) cslot = (int32_t)clk + lanes_below(fillm);
+                    clk += nfill;
+                } else {
+                    unsigned long long mm = fillm;
+                    while (mm) {
+                        const int k = __ffsll(mm) - 1;
+                        mm &= mm - 1;
+                        int32_t v;
+                        do {
+                            v = (int32_t)clk;
+                            clk = clk + 1 >= a.cache_slots ? 0 : clk + 1;
+                        } while (__ballot(lane < nS && hslot == v) != 0);
+                        if (lane == k) cslot = v;
+                    }
+                }
+                if (lane == 0) shClk = clk;
+            }
+        }
+        // (through LDS: every wave stages the columns, and nothing of this
+        // is held in registers through the matrix-core part)
+        shCol[lane] = col;
+        shCs[lane] = cslot;
+        shHs[lane] = hsrc;
+        if (lane == 0) {
+            shPath = path;
+            shFill = nfill;
+            shHit = nhit;
+        }
+    }
 
     // (10) K_SS.  CSR input: the working set by column (below).  Dense input: on the matrix cores (same operand
     // order as k_rows): the working-set rows pass through LDS in feature
@@ -728,7 +869,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // matrix-core waves accumulate the slice while the other waves copy it
     // to xS (the rows of the next k_rows).
     int csrE = 0;  // CSR: the columns of the working set's table
-    if (a.rp) {
+    if (CSR) {
         // CSR: the working set by column.  cidx[c] flags, then numbers in
         // increasing column order, the columns some sample holds; tab[e *
         // QS + s] = x_s[column e].  K_SS sums over the columns in that
@@ -1005,64 +1146,35 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
 
     if (wave != 0) {
         if (wave == 1 && (a.mode & SS_SOLVE) && !given) {
-            // The path of this iteration's row kernel (while wave 0
-            // solves): a working set whose samples are all cached is served
-            // from the cache; otherwise each missing sample gets a slot
-            // (FIFO, never a slot this working set reads) and the row
-            // kernel fills it.
-            int path = PATH_STREAM, nfill = 0;
-            int32_t cslot = -1;
-            if (use_cache) {
-                const int32_t hs = lane < nS ? hslot : -2;
-                const unsigned long long missm = __ballot(lane < nS && hs < 0);
-                int64_t clk = clk0;
-                // rows stop going to a cache that serves almost nothing (a
-                // working set whose samples rarely all recur): the fills
-                // cost HBM writes and the two paths give the same bits.  A
-                // cache with a slot for every sample never evicts, so it
-                // keeps filling: every working set whose samples have all
-                // been used before is then served.
-                const bool fill = a.cache_slots >= a.n || iter0 < 512 ||
-                                  c_served * 8 >= c_filled;
-                if (missm == 0) {
-                    path = PATH_CACHED;
-                    cslot = hs;
-                } else if (fill) {
-                    path = PATH_INSERT;
-                    unsigned long long mm = missm;
-                    while (mm) {
-                        const int k = __ffsll(mm) - 1;
-                        mm &= mm - 1;
-                        int32_t v;
-                        do {
-                            v = (int32_t)clk;
-                            clk = clk + 1 >= a.cache_slots ? 0 : clk + 1;
-                        } while (__ballot(lane < nS && hs == v) != 0);
-                        if (lane == k) cslot = v;
-                    }
-                    nfill = __popcll(missm);
-                    if (lane < nS && cslot >= 0) {
-                        const int32_t smp = shS[lane];
-                        const int32_t old = a.owner[cslot];
-                        if (old >= 0) a.slot_of[old] = -1;
-                        a.owner[cslot] = smp;
-                        a.slot_of[smp] = cslot;
-                    }
-                    if (lane == 0) *a.clock = clk;
+            // the cache's maps, and what the row kernel of this iteration
+            // computes and reads (while wave 0 solves)
+            const int path = shPath, nfill = shFill, nhit = shHit;
+            const int32_t cslot = shCs[lane], col = shCol[lane];
+            if (path == PATH_INSERT) {
+                if (cslot >= 0) {
+                    const int32_t old = a.owner[cslot];
+                    if (old >= 0) a.slot_of[old] = -1;
+                    a.owner[cslot] = col;
+                    a.slot_of[col] = cslot;
                 }
+                if (lane == 0) *a.clock = shClk;
             }
-            if (lane < nS) ws->cslot[lane] = cslot;
+            ws->cslot[lane] = cslot;
+            ws->hsrc[lane] = shHs[lane];
+            ws->colS[lane] = col;
+            ws->colq[lane] = col >= 0 ? a.sq[col] : 0.0f;
             if (lane == 0) {
                 ws->path = path;
                 const int64_t t = (iter0 + 1) % kPathLog;
                 ws->path_log[t] = (uint8_t)path;
                 ws->fill_log[t] = (uint8_t)nfill;
                 ws->ns_log[t] = (uint8_t)nS;
-                ws->cache_served = c_served + (path == PATH_CACHED ? nS : 0);
+                ws->hit_log[t] = (uint8_t)nhit;
+                ws->cache_served = c_served + (path == PATH_CACHED ? nS : nhit);
                 ws->cache_filled = c_filled + nfill;
             }
         }
-        if (a.rp && a.xsc) {
+        if (CSR && a.xsc) {
             // the CSR table and its columns for the row kernel (cidx and
             // tab are still in LDS)
             const int* cidx = reinterpret_cast<const int*>(xst);
@@ -1081,15 +1193,22 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         }
         const int ldp16 = (int)((ldp + 15) & ~(int64_t)15);
         const int W = a.slice;
-        if (!a.rp && W >= ldp16) {
+        if (!CSR && W >= ldp16 && !(spec && shPath == PATH_CACHED)) {
+            // the rows of the computed columns: a working-set slot's own
+            // from LDS, the others from X
             const int q4 = ldp16 >> 2, wst = W + 4;
-            for (int e = tid - 64; e < nS * q4; e += kSelThreads - 64) {
+            const int nc = spec ? 16 : nS;
+            for (int e = tid - 64; e < nc * q4; e += kSelThreads - 64) {
                 const int slot = e / q4, c4 = e - slot * q4;
-                const int64_t col = 4 * c4;
-                if (col < ldp)
+                const int64_t fc = 4 * c4;
+                const int32_t smp = shCol[slot];
+                if (fc < ldp && smp >= 0)
                     *reinterpret_cast<float4*>(a.xS + (int64_t)slot * ldp +
-                                               col) =
-                        ld4(xst + (pf ? shSlotCand[slot] : slot) * wst + 4 * c4);
+                                               fc) =
+                        slot < nS && smp == shS[slot]
+                            ? ld4(xst + (pf ? shSlotCand[slot] : slot) * wst +
+                                  4 * c4)
+                            : ld4(a.X + (int64_t)smp * ldp + fc);
             }
         }
         return;
@@ -1263,10 +1382,10 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     }
 }
 
-template <bool SVR, int NBLK>
+template <bool SVR, int NBLK, bool CSR>
 __global__ __launch_bounds__(kSelThreads) void k_select(SelArgs a)
 {
-    select_body<SVR, NBLK>(a);
+    select_body<SVR, NBLK, CSR>(a);
 }
 
 // One problem per block: several selections of problems that advance in
@@ -1278,27 +1397,27 @@ struct SelGroup {
 template <bool SVR>
 __global__ __launch_bounds__(kSelThreads) void k_select_group(SelGroup g)
 {
-    select_body<SVR, 1>(g.a[blockIdx.x]);
+    select_body<SVR, 1, false>(g.a[blockIdx.x]);
 }
 
-template <bool SVR, int NBLK>
+template <bool SVR, int NBLK, bool CSR>
 static void select_dispatch(const SelArgs& a, hipStream_t s, hipEvent_t e0,
                             hipEvent_t e1)
 {
     const size_t lds =
-        a.rp ? select_csr_lds_bytes(NBLK, a.ldp, a.csr_cols) +
-                   (select_csr_lists(NBLK, a.ldp, a.csr_cols)
-                        ? (size_t)a.csr_cols * 4
-                        : 0)
-             : select_lds_bytes(NBLK, a.slice);
-    if (!raise_dynamic_lds((const void*)k_select<SVR, NBLK>, lds))
+        CSR ? select_csr_lds_bytes(NBLK, a.ldp, a.csr_cols) +
+                  (select_csr_lists(NBLK, a.ldp, a.csr_cols)
+                       ? (size_t)a.csr_cols * 4
+                       : 0)
+            : select_lds_bytes(NBLK, a.slice);
+    if (!raise_dynamic_lds((const void*)k_select<SVR, NBLK, CSR>, lds))
         throw Error{SVM_E_UNSUPPORTED,
                     "select tile needs more LDS than the device allows"};
     if (e0 || e1)  // timed: the events are part of the dispatch
-        hipExtLaunchKernelGGL(k_select<SVR, NBLK>, dim3(1), dim3(kSelThreads),
-                              lds, s, e0, e1, 0, a);
+        hipExtLaunchKernelGGL((k_select<SVR, NBLK, CSR>), dim3(1),
+                              dim3(kSelThreads), lds, s, e0, e1, 0, a);
     else
-        k_select<SVR, NBLK><<<1, kSelThreads, lds, s>>>(a);
+        k_select<SVR, NBLK, CSR><<<1, kSelThreads, lds, s>>>(a);
 }
 
 void launch_select_group(const SelArgs* args, int P, bool svr, hipStream_t s)
@@ -1338,13 +1457,19 @@ void launch_select(const SelArgs& a0, int nblk_cols, bool svr, hipStream_t s,
             throw Error{SVM_E_UNSUPPORTED,
                         "too many features for a CSR working set in LDS"};
     }
-    switch (nblk_cols * 2 + (svr ? 1 : 0)) {
-        case 2: select_dispatch<false, 1>(a, s, e0, e1); break;
-        case 3: select_dispatch<true, 1>(a, s, e0, e1); break;
-        case 4: select_dispatch<false, 2>(a, s, e0, e1); break;
-        case 5: select_dispatch<true, 2>(a, s, e0, e1); break;
-        case 8: select_dispatch<false, 4>(a, s, e0, e1); break;
-        case 9: select_dispatch<true, 4>(a, s, e0, e1); break;
+    switch (nblk_cols * 4 + (svr ? 2 : 0) + (a.rp ? 1 : 0)) {
+        case 4: select_dispatch<false, 1, false>(a, s, e0, e1); break;
+        case 5: select_dispatch<false, 1, true>(a, s, e0, e1); break;
+        case 6: select_dispatch<true, 1, false>(a, s, e0, e1); break;
+        case 7: select_dispatch<true, 1, true>(a, s, e0, e1); break;
+        case 8: select_dispatch<false, 2, false>(a, s, e0, e1); break;
+        case 9: select_dispatch<false, 2, true>(a, s, e0, e1); break;
+        case 10: select_dispatch<true, 2, false>(a, s, e0, e1); break;
+        case 11: select_dispatch<true, 2, true>(a, s, e0, e1); break;
+        case 16: select_dispatch<false, 4, false>(a, s, e0, e1); break;
+        case 17: select_dispatch<false, 4, true>(a, s, e0, e1); break;
+        case 18: select_dispatch<true, 4, false>(a, s, e0, e1); break;
+        case 19: select_dispatch<true, 4, true>(a, s, e0, e1); break;
         default: throw Error{SVM_E_INTERNAL, "bad column-block count"};
     }
 }

@@ -393,6 +393,10 @@ Solver::Solver(Context& cx, const Features& f, const float* y_dev,
         throw Error{SVM_E_UNSUPPORTED,
                     "training set too large for the dense row kernel"};
     nb_ = (int)nb;
+    // Few blocks hold many rows each: a record per wave then leaves the
+    // selection fewer rows to look at again when a record is used up, and
+    // one record to each of its threads all the same.
+    sub_ = nb_ <= kSelThreads / 4 ? 4 : 1;
     ch_cap_ = sparse_chunk_cap(f);
 
     // One launch per outer iteration: as many k_iter blocks as are
@@ -445,8 +449,8 @@ Solver::Solver(Context& cx, const Features& f, const float* y_dev,
         xsc_cols_.alloc((size_t)f.ldp);
         xsc_.alloc((size_t)(f.ldp + 1) * kMaxQ);
     }
-    ckey_.alloc((size_t)nb_ * 2 * kBlockTop);
-    cidx_.alloc((size_t)nb_ * 2 * kBlockTop);
+    ckey_.alloc((size_t)nb_ * sub_ * 2 * kBlockTop);
+    cidx_.alloc((size_t)nb_ * sub_ * 2 * kBlockTop);
     if (fused_) {
         F2_.alloc((size_t)n_);
         irk_.alloc((size_t)2 * nbi_ * 2 * kBlockTop);
@@ -532,6 +536,7 @@ void Solver::launch_keys()
     a.kf = kf_;
     a.half = half_;
     a.tiles = tiles_;
+    a.sub = sub_;
     a.mode = RU_CAND;
     a.nS_override = 0;
     launch_rows(a, nb_, nblk_cols_, o_.type == SVM_EPS_SVR, cx_.stream);
@@ -559,6 +564,7 @@ void Solver::launch_keys_fused()
     a.kf = kf_;
     a.half = half_;
     a.tiles = tilesk_;
+    a.sub = 1;
     a.mode = RU_CAND;
     a.nS_override = 0;
     launch_rows(a, nbi_, 1, o_.type == SVM_EPS_SVR, cx_.stream);
@@ -586,6 +592,7 @@ void Solver::launch_hot_rows(hipEvent_t e0, hipEvent_t e1)
     a.kf = kf_;
     a.half = half_;
     a.tiles = tiles_;
+    a.sub = sub_;
     a.mode = RU_UPDATE | RU_CAND | RU_CHECK_DONE;
     a.nS_override = -1;
     if (cache_) {
@@ -601,7 +608,8 @@ void Solver::launch_solve(int32_t mode, hipEvent_t e0, hipEvent_t e1)
     SelArgs a{};
     a.cand_key = ckey_.p;
     a.cand_idx = cidx_.p;
-    a.nb = nb_;
+    a.nb = nb_ * sub_;
+    a.sub = sub_;
     a.half = half_;
     a.ws = ws_.p;
     a.alpha = alpha_.p;
@@ -626,7 +634,7 @@ void Solver::launch_solve(int32_t mode, hipEvent_t e0, hipEvent_t e1)
     a.max_inner = o_.max_inner;
     a.max_iter = o_.max_iter;
     a.mode = mode;
-    a.group_rows = (kRowThreads / 64) * 16 * tiles_;  // most rows of a block
+    a.group_rows = (kRowThreads / 64 / sub_) * 16 * tiles_;
     if (cache_) {
         a.cache = cache_->rows.p;
         a.ldc = cache_->ldc;
@@ -754,7 +762,8 @@ bool Solver::run_loop(SolveResult& r)
                     row_launches_ += 1;
                     row_rows_ += n_;
                     row_bytes_ += feat + (double)n_ * (per_row + 4.0 +
-                                                       4.0 * w.fill_log[t]);
+                                                       4.0 * w.fill_log[t] +
+                                                       4.0 * w.hit_log[t]);
                 }
             }
         }
@@ -1455,6 +1464,7 @@ std::vector<SolveResult> Solver::train_lockstep(
             a.max_iter = s.o_.max_iter;
             a.mode = SS_SOLVE | SS_CHECK_DONE;
             a.group_rows = kWaves * 16 * tiles;  // most rows of a block
+            a.sub = 1;
             hsel[q] = a;
         }
     };
@@ -1720,6 +1730,7 @@ void Solver::rows(const int32_t* samples, int32_t k, float* out_h)
     a.kf = kf_;
     a.half = half_;
     a.tiles = tiles_;
+    a.sub = sub_;
     a.mode = RU_ROWS;
     a.nS_override = k;
     if (rows_lds_bytes(nbc, f_.ldp, tiles_, o_.type == SVM_EPS_SVR,
@@ -1769,7 +1780,7 @@ void Solver::subproblem(const int32_t* B, int32_t nB, double inner_tol,
     a.max_inner = max_inner;
     a.max_iter = o_.max_iter;
     a.half = half_;
-    a.group_rows = (kRowThreads / 64) * 16 * tiles_;  // most rows of a block
+    a.group_rows = (kRowThreads / 64 / sub_) * 16 * tiles_;
     a.mode = SS_GIVEN_B | SS_SOLVE | SS_NO_WRITE;
     int nbc = nB <= 16 ? 1 : (nB <= 32 ? 2 : 4);
     launch_select(a, nbc, o_.type == SVM_EPS_SVR, s);
@@ -1816,7 +1827,7 @@ void Solver::apply(const int32_t* B, int32_t nB, const double* alpha_B)
     a.max_inner = 0;
     a.max_iter = o_.max_iter;
     a.half = half_;
-    a.group_rows = (kRowThreads / 64) * 16 * tiles_;  // most rows of a block
+    a.group_rows = (kRowThreads / 64 / sub_) * 16 * tiles_;
     a.mode = SS_GIVEN_B | SS_SOLVE | SS_SET_ALPHA;
     int nbc = nB <= 16 ? 1 : (nB <= 32 ? 2 : 4);
     launch_select(a, nbc, o_.type == SVM_EPS_SVR, s);
@@ -1840,6 +1851,7 @@ void Solver::apply(const int32_t* B, int32_t nB, const double* alpha_B)
     r.kf = kf_;
     r.half = half_;
     r.tiles = tiles_;
+    r.sub = sub_;
     r.mode = RU_UPDATE;
     r.nS_override = -1;
     if (rows_lds_bytes(nbc, f_.ldp, tiles_, o_.type == SVM_EPS_SVR,

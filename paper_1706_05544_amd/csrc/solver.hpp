@@ -320,6 +320,7 @@ private:
     int64_t n_, N_;
     KernelFn kf_;
     int half_, nblk_cols_, tiles_, nb_;
+    int sub_ = 1;  // candidate records of a k_rows block
     // one launch per outer iteration: blocks (= candidate records), tiles
     // per row wave, tiles of the record-writing k_rows launch on that grid;
     // the second responses buffer, the double-buffered records, the ticket

@@ -1,0 +1,53 @@
+"""Rows computed ahead for the kernel-row cache, and candidate records by wave.
+
+Where X is large (2^24 floats and more) the columns of a streaming launch
+that belong to cached samples compute rows that later working sets are
+likely to need, and the cached samples' rows are read.  K values are the
+same bits either way, so a training must give the bits of the one without
+the cache: with a cache that keeps everything, with one so small that it
+replaces rows all along, C-SVC and eps-SVR, another kernel, working sets
+below 16, features past one LDS slice of the selection (where no row is
+computed ahead), and shapes whose row kernel runs few blocks (a record per
+wave) or many.
+"""
+import numpy as np
+import pytest
+
+from paper_1706_05544_amd import native as nv
+
+pytestmark = pytest.mark.gpu
+
+
+def _data(n, d, svr=False):
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d), dtype=np.float32)
+    if svr:
+        z = np.sin(3 * X[:, 0]) + 0.1 * rng.standard_normal(n)
+        return X, z.astype(np.float32)
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    return X + np.float32(2.25 / np.sqrt(d)) * y[:, None], y
+
+
+@pytest.mark.parametrize("n,d,rows,kw", [
+    (40009, 420, 0, {}),                       # many blocks
+    (40009, 420, 90, {}),                      # constant replacement
+    (21001, 800, 0, {}),                       # a record per wave
+    (21001, 800, 200, dict(working_set=10)),
+    (21001, 801, 0, dict(kernel=1, coef0=1.0)),
+    (40000, 421, 0, dict(type=1, C=10.0, max_iter=400)),
+    (40000, 421, 70, dict(type=1, C=10.0, max_iter=400)),
+    (11000, 1600, 0, {}),                      # two slices
+])
+def test_same_bits_with_rows_computed_ahead(n, d, rows, kw):
+    X, y = _data(n, d, kw.get("type") == 1)
+    cache = rows * ((n + 3) // 4 * 4) * 4  # 0: the default (the whole K)
+    got = []
+    for cb in (-1, cache):
+        m = nv.svm_train(X, y, cache_bytes=cb, **kw)
+        got.append((m.info(), nv.svm_model_get(m, 0, with_alpha=True)[2]))
+    (i0, a0), (i1, a1) = got
+    np.testing.assert_array_equal(a1, a0)
+    for k in ("iters", "b", "dual_obj", "gap", "kernel_rows", "status"):
+        assert i1[k] == i0[k], k
+    assert i1["cache_fills"] > 0
+    assert i1["cache_hits"] <= i1["kernel_rows"]
