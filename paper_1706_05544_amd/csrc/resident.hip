@@ -175,58 +175,6 @@ __device__ __forceinline__ void agent_store(Glob<uint64_t> p, uint64_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// max of two values that are not NaN, in one instruction (fmax quiets each
-// operand first)
-__device__ __forceinline__ double max_f64(double a, double b)
-{
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-__device__ __forceinline__ double min_f64(double a, double b)
-{
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// every lane of each 16-lane row receives the row maximum
-__device__ __forceinline__ double rmax_f64(double v)
-{
-    v = max_f64(v, dpp_f64<kDppRor8>(v));
-    v = max_f64(v, dpp_f64<kDppRor4>(v));
-    v = max_f64(v, dpp_f64<kDppRor2>(v));
-    v = max_f64(v, dpp_f64<kDppRor1>(v));
-    return v;
-}
-
-// the rank of every entry of both sides' lists among its side's, and the
-// first `half` of each list into (ku, iu) and (kl, il): waves 0 .. 7 take
-// side 0, the others side 1, 16 lanes an entry
-__device__ __forceinline__ void rank_lists(const double (*k)[kResCand],
-                                           const int32_t (*i)[kResCand],
-                                           int M0, int M1, int half,
-                                           double* ku, int32_t* iu, double* kl,
-                                           int32_t* il, int tid)
-{
-    const int side = tid >> 9, l = tid & 15;
-    const int M = side ? M1 : M0;
-    for (int e = (tid & 511) >> 4; e < M; e += 32) {
-        const double ke = k[side][e];
-        const int32_t ie = i[side][e];
-        int c = 0;
-#pragma unroll 4
-        for (int f = l; f < M; f += 16)
-            c += better(k[side][f], i[side][f], ke, ie) ? 1 : 0;
-        c = row_sum_i32(c);
-        if (l == 0 && c < half) {
-            (side ? kl : ku)[c] = ke;
-            (side ? il : iu)[c] = ie;
-        }
-    }
-}
-
 // Blocks of a problem that start one launch must all be on the chip before
 // any of them waits for another: they count themselves in and go on only
 // when the last one has said so.  If they do not all arrive in time (other

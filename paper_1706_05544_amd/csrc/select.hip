@@ -49,26 +49,6 @@ __device__ __forceinline__ void var_scores(const SelArgs& a, int64_t t,
 constexpr int kSpec = 24;
 constexpr int64_t kSpecX = (int64_t)1 << 24;  // floats of X from which on
 
-// Best (key, lane) of each side over a 16-lane row (NBLK = 1) or the wave,
-// both sides interleaved; results are wave-uniform.  Ties go to the lowest
-// lane.
-template <int NBLK>
-__device__ __forceinline__ void best_two_sides(double& ku, int& lu, double& kl,
-                                               int& ll)
-{
-    if (NBLK == 1) {
-        const double mu = row_max_f64(ku), ml = row_max_f64(kl);
-        const int cu = row_min_i32(ku == mu ? lu : INT_MAX);
-        const int cl = row_min_i32(kl == ml ? ll : INT_MAX);
-        ku = rl_f64(mu, 0);
-        kl = rl_f64(ml, 0);
-        lu = rl_i32(cu, 0);
-        ll = rl_i32(cl, 0);
-    } else {
-        wave_best_pair(ku, lu, kl, ll);
-    }
-}
-
 // Features per LDS slice of the working-set rows in k_select.
 int select_slice(int nblk_cols, int64_t ldp)
 {
@@ -146,7 +126,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     constexpr int QS = NBLK * 16;  // slots covered by K_SS
     __shared__ double upk[kMaxHalf], lok[kMaxHalf];
     __shared__ int32_t upi[kMaxHalf], loi[kMaxHalf];
-    __shared__ double rmax[2][NW * 4];
+    __shared__ __align__(16) double rmax[2][NW * 4];
     __shared__ double theta[2];
     __shared__ double svk[2][kSurv];
     __shared__ int32_t svi[2][kSurv];
@@ -164,6 +144,8 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     __shared__ int32_t shPos[kMaxQ];  // position in B of the i-th smallest
     __shared__ float shsS[kMaxQ];
     __shared__ float KSS[QS][QS + 1];
+    // q <= 16: curvature of a pair of ranks and its reciprocal
+    __shared__ double2 shCur[NBLK == 1 ? 16 : 1][16];
     __shared__ double shDc[kMaxQ];
     __shared__ int32_t shNB, shNS, shGo, shDone;
     // the columns that the row kernel computes (see WorkingSet)
@@ -265,20 +247,43 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         double mu = -INFINITY, ml = -INFINITY;
 #pragma unroll
         for (int j = 0; j < kSelPerThread; ++j) {
-            mu = fmax(mu, ku[j]);
-            ml = fmax(ml, kl[j]);
+            mu = max_f64(mu, ku[j]);
+            ml = max_f64(ml, kl[j]);
         }
-        mu = row_max_f64(mu);
-        ml = row_max_f64(ml);
+        const double mu0 = mu, ml0 = ml;  // of this thread's records
+        mu = rmax_f64(mu);
+        ml = rmax_f64(ml);
         if ((lane & 15) == 0) {
             rmax[0][wave * 4 + (lane >> 4)] = mu;
             rmax[1][wave * 4 + (lane >> 4)] = ml;
         }
         if (tid < 2) nsv[tid] = 0;
         __syncthreads();
-        if (wave < 2) {
+        if (want <= 8 && a.nb >= 640) {
+            // ten waves or more hold records: the want-th largest of the
+            // waves' maxima, both sides in wave 0 (row 0 up, row 1 low, a
+            // lane a wave).  A looser bound (about 11 survivors a side
+            // instead of 9) in a third of the steps.
+            if (wave == 0) {
+                const double* rm = rmax[(lane >> 4) & 1] + 4 * (lane & 15);
+                const double2 x01 = *reinterpret_cast<const double2*>(rm);
+                const double2 x23 = *reinterpret_cast<const double2*>(rm + 2);
+                const double x = max_f64(max_f64(x01.x, x01.y),
+                                         max_f64(x23.x, x23.y));
+                int c = 1;
+                const int xlo = __double2loint(x), xhi = __double2hiint(x);
+                for_row_rotations([&](auto r) {
+                    constexpr int R = decltype(r)::value;
+                    const double o =
+                        __hiloint2double(row_rot<R>(xhi), row_rot<R>(xlo));
+                    c += o >= x ? 1 : 0;
+                });
+                const double th = rmax_f64(c >= want ? x : -INFINITY);
+                if ((lane & 15) == 0 && lane < 32) theta[lane >> 4] = th;
+            }
+        } else if (wave < 2) {
             // wave `side`, lane l: row maximum l of that side; theta = the
-            // largest x_l with at least `half` row maxima >= x_l (-inf if
+            // largest x_l with at least `want` row maxima >= x_l (-inf if
             // there is none)
             {
                 const int side = wave;
@@ -297,25 +302,29 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         t_c1 = wall_clock64();
         // (3) keep the candidates at or above the bound
         {
+            // (few threads hold any: those add themselves to the list)
             const double th0 = theta[0], th1 = theta[1];
+            if (mu0 != -INFINITY && mu0 >= th0) {
 #pragma unroll
-            for (int j = 0; j < kSelPerThread; ++j) {
-                for (int side = 0; side < 2; ++side) {
-                    const double kv = side ? kl[j] : ku[j];
-                    const int32_t iv = side ? il[j] : iu[j];
-                    const double th = side ? th1 : th0;
-                    const bool keep = kv != -INFINITY && kv >= th;
-                    const unsigned long long m = __ballot(keep);
-                    if (m == 0) continue;
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(&nsv[side], __popcll(m));
-                    base = __builtin_amdgcn_readfirstlane(base);
-                    const int pos = base + lanes_below(m);
-                    if (keep && pos < kSurv) {
-                        svk[side][pos] = kv;
-                        svi[side][pos] = iv;
+                for (int j = 0; j < kSelPerThread; ++j)
+                    if (ku[j] != -INFINITY && ku[j] >= th0) {
+                        const int pos = atomicAdd(&nsv[0], 1);
+                        if (pos < kSurv) {
+                            svk[0][pos] = ku[j];
+                            svi[0][pos] = iu[j];
+                        }
                     }
-                }
+            }
+            if (ml0 != -INFINITY && ml0 >= th1) {
+#pragma unroll
+                for (int j = 0; j < kSelPerThread; ++j)
+                    if (kl[j] != -INFINITY && kl[j] >= th1) {
+                        const int pos = atomicAdd(&nsv[1], 1);
+                        if (pos < kSurv) {
+                            svk[1][pos] = kl[j];
+                            svi[1][pos] = il[j];
+                        }
+                    }
             }
         }
         __syncthreads();
@@ -585,8 +594,9 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
 
     // (8) working set, distinct samples (wave 0, lane-parallel)
     if (wave == 0) {
-        int go = 0, nB = 0;
+        int go = 0, nB = 0, nS = 0;
         double gap = 0.0;
+        bool built = false;  // slots and order by index made already
         if (!given) {
             const bool valid = upk[0] != -INFINITY && lok[0] != -INFINITY;
             const double m = upk[0], M = -lok[0];
@@ -605,7 +615,72 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
                 shMx = valid ? m : 0.0;
                 shMn = valid ? M : 0.0;
             }
-            if (build) {
+            if (build && NBLK == 1) {
+                // Both lists in one 16-lane row, a candidate a lane: the 15
+                // row rotations meet every other one, and what the working
+                // set needs of a pair is taken in that one pass (equal
+                // variable, lower index, the other copy of the sample).
+                const int c = lane & 15;
+                const bool isU = c < half;
+                const int k = isU ? c : c - half;
+                const bool inl = c < 2 * half;
+                const double key = !inl ? -INFINITY : isU ? upk[k] : lok[k];
+                const bool ent = key != -INFINITY;
+                const int32_t idx = !ent ? INT_MAX : isU ? upi[k] : loi[k];
+                const int32_t smp = ent ? (int32_t)sample_of(SVR, idx, n) : -1;
+                // a variable placed earlier in the order U0 L0 U1 L1 ...: up
+                // entry k follows low entries 0 .. k - 1, low entry k up
+                // entries 0 .. k
+                const uint32_t before =
+                    isU ? ((1u << k) - 1u) << half : (2u << k) - 1u;
+                uint32_t eqm = 0, ltm = 0, twm = 0;
+                for_row_rotations([&](auto r) {
+                    constexpr int R = decltype(r)::value;
+                    const int32_t im = row_rot<R>(idx);
+                    const uint32_t bit = 1u << ((c - R) & 15);
+                    eqm |= im == idx ? bit : 0u;
+                    ltm |= im < idx ? bit : 0u;
+                    if (SVR) twm |= row_rot<R>(smp) == smp ? bit : 0u;
+                });
+                const bool keep = ent && !(eqm & before);
+                const uint32_t keepm = (uint32_t)__ballot(keep) & 0xffffu;
+                const uint32_t km = keepm & ((1u << half) - 1u);
+                const uint32_t lm = keepm >> half;
+                const uint32_t below = (1u << k) - 1u;
+                int pos = __popc(km & below) + __popc(lm & below);
+                if (!isU) pos += (int)((km >> k) & 1u);
+                nB = __popc(keepm);
+                // slot: the samples in the order of B; the second of two
+                // copies of a sample shares the slot of the first
+                int slot = pos;
+                uint32_t secm = 0;
+                if (SVR) {
+                    const uint32_t tw = twm & keepm;  // its twin, if any
+                    const int tpos = __shfl(pos, tw ? __builtin_ctz(tw) : c);
+                    const bool second = keep && tw && tpos < pos;
+                    secm = (uint32_t)__ballot(second) & 0xffffu;
+                    if (second) slot = tpos;
+                    int drop = 0;  // seconds placed before the slot's first
+                    for (uint32_t q = secm; q; q &= q - 1)
+                        drop += rl_i32(pos, __builtin_ctz(q)) < slot ? 1 : 0;
+                    slot -= drop;
+                }
+                nS = nB - __popc(secm);
+                if (keep && lane < 16) {
+                    if (a.mode & SS_SOLVE) {
+                        shB[pos] = idx;
+                        shSlot[pos] = slot;
+                        shPos[__popc(ltm & keepm)] = pos;
+                        shS[slot] = smp;
+                        shSlotCand[slot] = c;
+                    } else {
+                        ws->B[pos] = idx;
+                    }
+                }
+                built = true;
+                if (a.mode & SS_SOLVE) go = 1;
+                else if (lane == 0) ws->nB = nB;
+            } else if (build) {
                 // lanes [0,half): up list, [half,2half): low list; position
                 // in the interleaved order U0 L0 U1 L1 ...
                 const bool isU = lane < half;
@@ -619,27 +694,11 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
                 // drop a variable already placed earlier in the order: up
                 // entry k follows low entries 0..k-1, low entry k follows up
                 // entries 0..k (entries compared through registers)
-                if (2 * half <= 16) {
-                    // both lists in the first 16-lane row: each lane meets
-                    // every other entry by the 15 row rotations (no chain
-                    // of readlanes)
-                    int dup = 0;
-                    const int lo = isU ? half : 0;  // partners it checks:
-                    const int hi = isU ? half + k : k + 1;  // lanes [lo, hi)
-                    for_row_rotations([&](auto r) {
-                        constexpr int R = decltype(r)::value;
-                        const int m = row_rot<R>(lane & 15);
-                        const int32_t im = row_rot<R>(idx);
-                        dup |= (m >= lo && m < hi && im == idx) ? 1 : 0;
-                    });
-                    if (dup) keep = false;
-                } else {
-                    for (int j = 0; j < half; ++j) {
-                        const int32_t uj = rl_i32(idx, j),
-                                      lj = rl_i32(idx, half + j);
-                        if (isU && j < k && lj == idx) keep = false;
-                        if (inL && j <= k && uj == idx) keep = false;
-                    }
+                for (int j = 0; j < half; ++j) {
+                    const int32_t uj = rl_i32(idx, j),
+                                  lj = rl_i32(idx, half + j);
+                    if (isU && j < k && lj == idx) keep = false;
+                    if (inL && j <= k && uj == idx) keep = false;
                 }
                 const unsigned long long m = __ballot(keep);
                 const unsigned long long mu = m & ((1ull << half) - 1ull);
@@ -661,8 +720,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
             go = (a.mode & SS_SOLVE) ? 1 : 0;
         }
         __builtin_amdgcn_wave_barrier();
-        int nS = 0;
-        if (go) {
+        if (go && !built) {
             // slot of each variable: rank of the first occurrence of its
             // sample (eps-SVR: both copies of a sample share one slot)
             const bool act = lane < nB;
@@ -1231,92 +1289,120 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     const double a0 = al;
     if ((a.mode & SS_SET_ALPHA) && act) al = ws->alphaB[bpos];
     const double C = a.C;
-    const double itol = a.inner_tol_override >= 0.0
-                            ? a.inner_tol_override
-                            : fmax(a.inner_ratio * shGap, 0.5 * a.tol);
-    // q <= 16: each lane holds the K_SS row of its slot in registers, and
-    // a step takes K(s, s_i), K(s, s_j) from there (uniform register
-    // index) and K_ii, K_jj, K_ij from lanes i and j: the same stored
-    // values as the LDS reads, without an LDS round trip on the step's
-    // chain
-    float krow[DUP ? QS : 1];
-    if (DUP) {
-#pragma unroll
-        for (int c = 0; c < QS; ++c) krow[c] = KSS[sl][c];
-    }
+    const double itol =
+        uniform_f64(a.inner_tol_override >= 0.0
+                        ? a.inner_tol_override
+                        : fmax(a.inner_ratio * shGap, 0.5 * a.tol));
     int steps = 0;
-    for (; steps < a.max_inner; ++steps) {
-        const bool up = act && ((yv > 0 && al < C) || (yv < 0 && al > 0));
-        const bool lo = act && ((yv > 0 && al > 0) || (yv < 0 && al < C));
-        double bu, bl;
-        int Li, Lj;
-        if (DUP) {
-            // row 0: up scores v, row 1: low scores -v; ties to the lowest
-            // lane = the lowest index
-            const bool lside = prow == 1;
-            const double key =
-                lside ? (lo ? -v : -INFINITY) : (up ? v : -INFINITY);
-            const int idx = (lside ? lo : up) ? p : INT_MAX;
-            const double M = row_max_f64(key);
-            const unsigned long long hit = __ballot(key == M && idx != INT_MAX);
-            bu = rl_f64(M, 0);
-            bl = rl_f64(M, 16);
-            Li = __builtin_ctzll((hit & 0xFFFFull) | 0x10000ull);
-            Lj = __builtin_ctzll(((hit >> 16) & 0xFFFFull) | 0x10000ull);
-        } else {
-            bu = up ? v : -INFINITY;
-            bl = lo ? -v : -INFINITY;
-            Li = up ? lane : INT_MAX;
-            Lj = lo ? lane : INT_MAX;
+    if constexpr (DUP) {
+        // The variable of rank p sits in lane p of row 0 (its up side: w =
+        // v) and of row 1 (its low side: w = -v).  A lone wave issues an
+        // instruction every 4 ns or so whatever it is, so a step is as long
+        // as its instruction count: the lane's row of K by rank in registers
+        // (negated in row 1, whose w moves the other way), the curvature of
+        // every pair and its reciprocal (refined twice, as a division does
+        // it) in a table that the four rows of the wave fill, one comparison
+        // for each side's room, the clipping as minima.  0.43 -> 0.25 us a
+        // step, the same bits.
+        const bool low = prow == 1;
+        const bool pos = yv > 0;
+        const double Cl = act ? C : 0.0;  // (no room in unused lanes)
+        if (!act) al = 0.0;
+        double w = low ? -v : v;
+        float krow[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            const float k = KSS[sl][rl_i32(sl, c)];
+            krow[c] = low ? -k : k;
+        }
+        {
+            const int slp = __shfl(sl, p);  // rows 2 and 3: row 0's slots
+            const float kpp = KSS[slp][slp];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int slc = __shfl(sl, 4 * prow + i);
+                double a2 = fma(-2.0, (double)KSS[slp][slc],
+                                (double)kpp + (double)KSS[slc][slc]);
+                if (a2 <= 0.0) a2 = kTau;
+                double y = __builtin_amdgcn_rcp(a2);
+                y = fma(y, fma(-a2, y, 1.0), y);
+                y = fma(y, fma(-a2, y, 1.0), y);
+                shCur[p][4 * prow + i] = make_double2(a2, y);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        const bool fromC = pos != low;
+        while (steps < a.max_inner) {
+            const double cap = fromC ? Cl - al : al;
+            const bool has = cap > 0.0;
+            const double kx = has ? w : -INFINITY;
+            const double Mx = rmax_f64(kx);
+            const unsigned long long hit = __ballot(has && kx == Mx);
+            const double diff = rl_f64(Mx, 0) + rl_f64(Mx, 16);
+            if (!(diff > itol)) break;  // (-inf: a side has no variable)
+            const int Li = __builtin_ctzll(hit);  // lowest lane = index
+            const int Lj = __builtin_ctzll(hit >> 16) & 15;
+            const double2 cur = shCur[Li][Lj];
+            const double Ui = rl_f64(cap, Li), Lb = rl_f64(cap, 16 + Lj);
+            const double dk = (double)krow[Li] - (double)krow[Lj];
+            const double q0 = diff * cur.y;
+            double s = fma(fma(-cur.x, q0, diff), cur.y, q0);
+            s = min_f64(min_f64(s, Ui), Lb);
+            w = fma(-dk, s, w);
+            const bool isI = p == Li;
+            const double an = fma(isI ? yv : -yv, s, al);
+            const bool clip = (isI ? Ui : Lb) == s;
+            const double bound = isI == pos ? Cl : 0.0;
+            if (isI || p == Lj) al = clip ? bound : an;
+            ++steps;
+        }
+    } else {
+        for (; steps < a.max_inner; ++steps) {
+            const bool up = act && ((yv > 0 && al < C) || (yv < 0 && al > 0));
+            const bool lo = act && ((yv > 0 && al > 0) || (yv < 0 && al < C));
+            double bu = up ? v : -INFINITY;
+            double bl = lo ? -v : -INFINITY;
+            int Li = up ? lane : INT_MAX;
+            int Lj = lo ? lane : INT_MAX;
             wave_best_pair(bu, Li, bl, Lj);
+            if (bu == -INFINITY || bl == -INFINITY) break;
+            const double vi = bu, vj = -bl;
+            if (!(vi - vj > itol)) break;
+            // the room of each lane's variable as the up one (ucap) and as
+            // the low one (lcap), taken from lanes i and j; lanes i and j
+            // update their own alpha with their own label
+            const double ucap = yv > 0 ? C - al : al;
+            const double lcap = yv > 0 ? al : C - al;
+            const double Ui = rl_f64(ucap, Li), Lb = rl_f64(lcap, Lj);
+            const int si = rl_i32(sl, Li), sj = rl_i32(sl, Lj);
+            const double kij = (double)KSS[si][sj];
+            const double kai = (double)KSS[sl][si];
+            const double kaj = (double)KSS[sl][sj];
+            const double kii = (double)KSS[si][si];
+            const double kjj = (double)KSS[sj][sj];
+            double a2 = kii + kjj - 2.0 * kij;
+            if (a2 <= 0.0) a2 = kTau;
+            double s = (vi - vj) / a2;
+            bool ci = false, cj = false;
+            if (Ui <= s) {
+                s = Ui;
+                ci = true;
+            }
+            if (Lb <= s) {
+                s = Lb;
+                cj = true;
+                ci = (Ui == s);
+            }
+            if (act && p == Li) {
+                al += yv * s;
+                if (ci) al = yv > 0 ? C : 0.0;
+            }
+            if (act && p == Lj) {
+                al -= yv * s;
+                if (cj) al = yv > 0 ? 0.0 : C;
+            }
+            if (act) v -= s * (kai - kaj);
         }
-        if (bu == -INFINITY || bl == -INFINITY) break;
-        const double vi = bu, vj = -bl;
-        if (!(vi - vj > itol)) break;
-        // the room of each lane's variable as the up one (ucap) and as the
-        // low one (lcap), taken from lanes i and j; lanes i and j update
-        // their own alpha with their own label
-        const double ucap = yv > 0 ? C - al : al;
-        const double lcap = yv > 0 ? al : C - al;
-        const double Ui = rl_f64(ucap, Li), Lb = rl_f64(lcap, Lj);
-        const int si = rl_i32(sl, Li), sj = rl_i32(sl, Lj);
-        double kij, kai, kaj, kii, kjj;
-        if (DUP) {
-            const float fi = krow[si], fj = krow[sj];  // K(s, s_i), K(s, s_j)
-            kai = (double)fi;
-            kaj = (double)fj;
-            kij = (double)__int_as_float(rl_i32(__float_as_int(fj), Li));
-            kii = (double)__int_as_float(rl_i32(__float_as_int(fi), Li));
-            kjj = (double)__int_as_float(rl_i32(__float_as_int(fj), Lj));
-        } else {
-            kij = (double)KSS[si][sj];
-            kai = (double)KSS[sl][si];
-            kaj = (double)KSS[sl][sj];
-            kii = (double)KSS[si][si];
-            kjj = (double)KSS[sj][sj];
-        }
-        double a2 = kii + kjj - 2.0 * kij;
-        if (a2 <= 0.0) a2 = kTau;
-        double s = (vi - vj) / a2;
-        bool ci = false, cj = false;
-        if (Ui <= s) {
-            s = Ui;
-            ci = true;
-        }
-        if (Lb <= s) {
-            s = Lb;
-            cj = true;
-            ci = (Ui == s);
-        }
-        if (act && p == Li) {
-            al += yv * s;
-            if (ci) al = yv > 0 ? C : 0.0;
-        }
-        if (act && p == Lj) {
-            al -= yv * s;
-            if (cj) al = yv > 0 ? 0.0 : C;
-        }
-        if (act) v -= s * (kai - kaj);
     }
     const uint64_t t_inner = wall_clock64();
 

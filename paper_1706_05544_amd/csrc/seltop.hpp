@@ -10,6 +10,32 @@
 
 namespace msvm {
 
+// max of two values that are not NaN, in one instruction (fmax quiets each
+// operand first)
+__device__ __forceinline__ double max_f64(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+__device__ __forceinline__ double min_f64(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// every lane of each 16-lane row receives the row maximum
+__device__ __forceinline__ double rmax_f64(double v)
+{
+    v = max_f64(v, dpp_f64<kDppRor8>(v));
+    v = max_f64(v, dpp_f64<kDppRor4>(v));
+    v = max_f64(v, dpp_f64<kDppRor2>(v));
+    v = max_f64(v, dpp_f64<kDppRor1>(v));
+    return v;
+}
+
 // Survivor-list capacity per side of the threshold filter.
 constexpr int kSurv = 1024;
 
@@ -111,6 +137,33 @@ __device__ __forceinline__ void pair_rank_top(const double (*k)[kSurv],
     }
 }
 
+// the rank of every entry of both sides' lists among its side's, and the
+// first `half` of each list into (ku, iu) and (kl, il): waves 0 .. 7 take
+// side 0, the others side 1, 16 lanes an entry
+template <int CAP>
+__device__ __forceinline__ void rank_lists(const double (*k)[CAP],
+                                           const int32_t (*i)[CAP],
+                                           int M0, int M1, int half,
+                                           double* ku, int32_t* iu, double* kl,
+                                           int32_t* il, int tid)
+{
+    const int side = tid >> 9, l = tid & 15;
+    const int M = side ? M1 : M0;
+    for (int e = (tid & 511) >> 4; e < M; e += 32) {
+        const double ke = k[side][e];
+        const int32_t ie = i[side][e];
+        int c = 0;
+#pragma unroll 4
+        for (int f = l; f < M; f += 16)
+            c += better(k[side][f], i[side][f], ke, ie) ? 1 : 0;
+        c = row_sum_i32(c);
+        if (l == 0 && c < half) {
+            (side ? kl : ku)[c] = ke;
+            (side ? il : iu)[c] = ie;
+        }
+    }
+}
+
 // Exact top `half` of each side's entries (k[s][0..M_s), i[s][0..M_s)),
 // M_s <= kSurv, into (ku, iu) and (kl, il).  A list longer than one pair
 // pass ranks cheaply is cut first: the half-th best of its first 64
@@ -161,7 +214,7 @@ __device__ __forceinline__ void top_half(double (*k)[kSurv], int32_t (*i)[kSurv]
     }
     const int lm = max(M0, M1);
     if (lm <= kPairSmall) {
-        pair_rank_top<16>(k, i, M0, M1, half, ku, iu, kl, il, tid);
+        rank_lists(k, i, M0, M1, half, ku, iu, kl, il, tid);
     } else if (lm <= 2 * kPairSmall) {
         pair_rank_top<8>(k, i, M0, M1, half, ku, iu, kl, il, tid);
     } else {
