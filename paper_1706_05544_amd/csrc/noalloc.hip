@@ -13,6 +13,7 @@
 #include <cstdint>
 #include <mutex>
 
+#include "predict.hpp"
 #include "solver.hpp"
 
 namespace msvm {
@@ -81,17 +82,26 @@ void predict_noalloc(const svm_model& mdl, const float* X, int64_t m,
         throw Error{SVM_E_UNSUPPORTED,
                     "a row of X does not fit the 32 MiB staging array"};
     int32_t* bad = reinterpret_cast<int32_t*>(base);  // never read
+    // the array: norms, then the kernel values of the path for few rows, if
+    // it is taken and they fit, or the partial sums, then the staged rows
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    int64_t few =
+        m <= chunk ? predict_few_floats(mdl.n_sv, m, ldp) : (int64_t)0;
+    if (kScratchHead + up((size_t)m * 4) + up((size_t)few * 4) +
+            (copy ? (size_t)m * ldp * 4 : 0) >
+        kScratchBytes)
+        few = 0;
+    const int64_t most = few > 0 ? m : chunk;  // rows at a time
+    const size_t sq_bytes = up((size_t)most * 4);
+    const size_t mid_bytes =
+        up(few > 0
+               ? (size_t)few * 4
+               : (size_t)predict_part_doubles(mdl.n_sv, chunk, mdl.n_out) * 8);
     float* sq = reinterpret_cast<float*>(base + kScratchHead);
-    const size_t sq_bytes = ((size_t)chunk * 4 + 255) & ~(size_t)255;
-    const size_t part_bytes =
-        ((size_t)predict_part_doubles(mdl.n_sv, chunk, mdl.n_out) * 8 + 255) &
-        ~(size_t)255;
-    double* part =
-        reinterpret_cast<double*>(base + kScratchHead + sq_bytes);
-    float* rows = reinterpret_cast<float*>(base + kScratchHead + sq_bytes +
-                                           part_bytes);
-    if (kScratchHead + sq_bytes + part_bytes +
-            (copy ? (size_t)chunk * ldp * 4 : 0) >
+    unsigned char* mid = base + kScratchHead + sq_bytes;
+    float* rows = reinterpret_cast<float*>(mid + mid_bytes);
+    if (kScratchHead + sq_bytes + mid_bytes +
+            (copy ? (size_t)most * ldp * 4 : 0) >
         kScratchBytes)
         throw Error{SVM_E_INTERNAL, "staging layout"};
 
@@ -107,7 +117,8 @@ void predict_noalloc(const svm_model& mdl, const float* X, int64_t m,
     a.kf = mdl.kf;
     a.ldp = ldp;
     a.nrange = predict_ranges(mdl.n_sv);
-    a.part = a.nrange > 1 ? part : nullptr;
+    a.part = a.nrange > 1 && few == 0 ? reinterpret_cast<double*>(mid)
+                                      : nullptr;
     for (int64_t r0 = 0; r0 < m; r0 += chunk) {
         const int64_t k = m - r0 < chunk ? m - r0 : chunk;
         const float* src = X + r0 * ld;
@@ -125,7 +136,10 @@ void predict_noalloc(const svm_model& mdl, const float* X, int64_t m,
         a.m = k;
         a.row_base = r0;
         a.out = out + r0 * mdl.n_out;
-        launch_predict(a, s);
+        if (few > 0)
+            launch_predict_few(a, reinterpret_cast<float*>(mid), s);
+        else
+            launch_predict(a, s);
     }
     if (mdl.scaled && mdl.type == SVM_EPS_SVR && mdl.y_sd > 0.0)
         launch_affine(out, m * mdl.n_out, mdl.y_sd, mdl.y_mu, s);

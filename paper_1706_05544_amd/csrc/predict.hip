@@ -22,8 +22,12 @@
 
 #include "common.hpp"
 #include "device.hpp"
+#include "predict.hpp"
 
 namespace msvm {
+
+// features of a row whose tiles are read at 32-bit offsets
+constexpr int64_t kFewMaxLdp = (int64_t)1 << 20;
 
 constexpr int kPredDK = 64;            // features per LDS chunk
 constexpr int kPredLS = kPredDK + 4;   // padded LDS row stride
@@ -405,6 +409,228 @@ void launch_predict(const PredictArgs& a, hipStream_t s)
         k_predict_sum<<<blocks, 256, 0, s>>>(a.part, a.nrange, mn, a.n_out,
                                              a.b, a.out);
     }
+}
+
+// ---------------------------------------------------------------------------
+// few query rows
+// ---------------------------------------------------------------------------
+//
+// A block of the kernels above walks some 25 support tiles one after another
+// (about 3.5 us each when it is alone on its compute unit), and a batch of
+// 16 rows against 3000 support rows has two such blocks.  Here the chip is
+// filled from both sides: k_predict_k computes the kernel values of all
+// (query, support) tiles at once into a buffer, and k_predict_ksum adds
+// c_j K, a query row a block.  Lane nl of a range takes the range's support
+// rows nl, nl + 16, ... in order, the lanes are added by the same tree and
+// the ranges in the same order as above: the same bits, so which path a
+// call takes shows in its time only.  What bounds it is latency: the norms,
+// the values and the sums are three dependent launches, each one or two
+// round trips to memory long.  svm_predict_noalloc, us, one kernel -> this:
+// 16 x 128 against 3000 support rows 87.6 -> 30.7, 300 x 128 88.4 -> 39.6,
+// 16 x 784 against 12000 868 -> 63, 1000 x 784 against 3000 with 10 outputs
+// 957 -> 139.
+
+// The path is taken
+// - below kFewBlocks blocks of the one-kernel path (half the compute units);
+// - where a block's chain of tiles is long enough (tiles x (4 + 16-feature
+//   chunks), about half a microsecond each) to pay for the second launch:
+//   300 support rows x 20 (30 units) take 20 us either way, 700 x 20 (66)
+//   gain (29 -> 19 us for 16 rows);
+// - up to 2^14 kernel values for a unit of that chain (700 x 20 against
+//   1000 rows, 0.7 M values, 30 -> 22 us; at 2.8 M 33 -> 48) and up to
+//   kFewFloats kernel values (16 MB), whose traffic then eats the
+//   gain: 1500 x 128 against 2000 rows (3 M values) 87 -> 57 us, 3000
+//   against 1000 89 -> 56, at 6 M it is lost; wider rows, whose one-kernel
+//   chain grows with the features, up to four times that (3000 x 784
+//   against 4000 rows, 12 M: 940 -> 450 us).
+constexpr int64_t kFewBlocks = 128;
+constexpr int64_t kFewTileWork = 40;
+constexpr int64_t kFewFloats = (int64_t)1 << 22;
+
+// T x T matrix-core tiles a wave; a block is 16 x 64 (T = 1) or 64 x 64.
+template <int T>
+__global__ __launch_bounds__(256) void k_predict_k(PredictArgs a, float* K,
+                                                   int64_t kst)
+{
+    constexpr int U = T == 1 ? 4 : 2;  // 16-feature chunks in flight
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, nl = lane & 15;
+    const int ldp = (int)a.ldp;
+    const int64_t m = a.m, nsv = a.nsv;
+    const int64_t q0 = T == 1 ? (int64_t)blockIdx.x * 16
+                              : (int64_t)blockIdx.x * 64 + 32 * (wave >> 1);
+    const int64_t s0 = (int64_t)blockIdx.y * 64 +
+                       (T == 1 ? 16 * wave : 32 * (wave & 1));
+    if (q0 >= m || s0 >= nsv) return;
+    const Rsrc rA = make_rsrc(a.Xt + q0 * ldp,
+                              min((int64_t)(16 * T), m - q0) * ldp * 4);
+    const Rsrc rB = make_rsrc(a.SV + s0 * ldp,
+                              min((int64_t)(16 * T), nsv - s0) * ldp * 4);
+    float4 av[2][U][T], bv[2][U][T];
+    auto fetch = [&](int c0, float4 (&x)[U][T], float4 (&y)[U][T]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = 16 * (c0 + u) + 4 * g;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint32_t o =
+                    col < ldp ? (uint32_t)(((16 * t + nl) * ldp + col) * 4)
+                              : kOob;
+                x[u][t] = bld_f4(rA, o);
+                y[u][t] = bld_f4(rB, o);
+            }
+        }
+    };
+    fetch(0, av[0], bv[0]);
+    // the epilogue's data lands during the products
+    float sqr[T][4], ssv[T];
+    int64_t stn[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int64_t j = s0 + 16 * t + nl;
+        ssv[t] = j < nsv ? a.sqsv[j] : 0.0f;
+        stn[t] = (a.self_match && j < nsv) ? a.sv_train_idx[j] : -1;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t r = q0 + 16 * t + 4 * g + v;
+            sqr[t][v] = r < m ? a.sqt[r] : 0.0f;
+        }
+    }
+    floatx4 acc[T][T];
+#pragma unroll
+    for (int r = 0; r < T; ++r)
+#pragma unroll
+        for (int c = 0; c < T; ++c) acc[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int nch = (ldp + 15) >> 4;
+    auto step = [&](int c0, const float4 (&x)[U][T], const float4 (&y)[U][T]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + u < nch) {  // uniform
+#pragma unroll
+                for (int r = 0; r < T; ++r)
+#pragma unroll
+                    for (int c = 0; c < T; ++c)
+                        acc[r][c] = mfma_chunk(acc[r][c], x[u][r], y[u][c]);
+            }
+    };
+    for (int c0 = 0; c0 < nch; c0 += 2 * U) {
+        fetch(c0 + U, av[1], bv[1]);  // (zeros past the last chunk)
+        step(c0, av[0], bv[0]);
+        fetch(c0 + 2 * U, av[0], bv[0]);
+        step(c0 + U, av[1], bv[1]);
+    }
+#pragma unroll
+    for (int r = 0; r < T; ++r)
+#pragma unroll
+        for (int c = 0; c < T; ++c) {
+            const int64_t j = s0 + 16 * c + nl;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t i = q0 + 16 * r + 4 * g + v;
+                float kv = kernel_from_dot(a.kf, sqr[r][v], ssv[c],
+                                           acc[r][c][v]);
+                if (a.kf.kind == SVM_KERNEL_RBF && stn[c] == i + a.row_base)
+                    kv = 1.0f;
+                if (i < m && j < kst) K[i * kst + j] = kv;
+            }
+        }
+}
+
+// One query row a block, 16 lanes a range of support rows.
+template <int NOUT>
+__global__ __launch_bounds__(128) void k_predict_ksum(PredictArgs a,
+                                                      const float* K,
+                                                      int64_t kst)
+{
+    constexpr int U = NOUT == 1 ? 16 : NOUT == 4 ? 8 : 2;
+    __shared__ double sh[8][NOUT];
+    const int tid = threadIdx.x, r = tid >> 4, nl = tid & 15;
+    const int n_out = a.n_out;
+    const int64_t row = blockIdx.x, nsv = a.nsv;
+    if (r < a.nrange) {
+        int64_t lo, hi;
+        predict_range_of(nsv, a.nrange, r, lo, hi);
+        const float* kr = K + row * kst;
+        double part[NOUT];
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) part[o] = 0.0;
+        for (int64_t s0 = lo + nl; s0 < hi; s0 += 16 * U) {
+            float kv[U];
+            double cf[U][NOUT];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t j = s0 + 16 * u;
+                const bool ok = j < hi;
+                kv[u] = ok ? kr[j] : 0.0f;
+#pragma unroll
+                for (int o = 0; o < NOUT; ++o)
+                    cf[u][o] = (ok && o < n_out) ? a.coef[j * n_out + o] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int o = 0; o < NOUT; ++o)
+                    part[o] = fma(cf[u][o], (double)kv[u], part[o]);
+        }
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) {
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1)
+                part[o] += __shfl_xor(part[o], off, 16);
+            if (nl == 0) sh[r][o] = part[o];
+        }
+    }
+    __syncthreads();
+    if (tid < n_out) {
+        double v = sh[0][tid];
+        if (a.nrange > 1) {
+            v = 0.0;
+            for (int q = 0; q < a.nrange; ++q) v += sh[q][tid];
+        }
+        a.out[row * n_out + tid] = v + (a.b ? a.b[tid] : 0.0);
+    }
+}
+
+int64_t predict_few_floats(int64_t nsv, int64_t m, int64_t ldp)
+{
+    const int64_t nr = predict_ranges(nsv);
+    const int64_t blocks = (m + 63) / 64 * nr;
+    const int64_t tiles = ((nsv + 63) / 64 + nr - 1) / nr;
+    const int64_t kst = (nsv + 15) & ~(int64_t)15;
+    const int64_t work = tiles * (4 + (ldp + 15) / 16);
+    const int64_t most = std::min(
+        work << 14,
+        kFewFloats * std::max<int64_t>(1, std::min<int64_t>(4, ldp / 128)));
+    if (m <= 0 || nsv <= 0 || ldp > kFewMaxLdp || blocks >= kFewBlocks ||
+        work < kFewTileWork || kst > most / m)
+        return 0;
+    return m * kst;
+}
+
+void launch_predict_few(const PredictArgs& a, float* kbuf, hipStream_t s)
+{
+    if (a.nrange != predict_ranges(a.nsv) || !kbuf ||
+        predict_few_floats(a.nsv, a.m, a.ldp) <= 0 || a.n_out < 1)
+        throw Error{SVM_E_INTERNAL, "decision of few rows"};
+    if (a.n_out > 16)
+        throw Error{SVM_E_UNSUPPORTED, "more than 16 outputs"};
+    const int64_t kst = (a.nsv + 15) & ~(int64_t)15;
+    const unsigned gs = (unsigned)((a.nsv + 63) / 64);
+    const int64_t t16 = (a.m + 15) / 16;
+    // one matrix-core tile a wave until that makes 4 waves a SIMD
+    if (t16 * gs <= 1024)
+        k_predict_k<1><<<dim3((unsigned)t16, gs), 256, 0, s>>>(a, kbuf, kst);
+    else
+        k_predict_k<2><<<dim3((unsigned)((a.m + 63) / 64), gs), 256, 0, s>>>(
+            a, kbuf, kst);
+    const unsigned rows = (unsigned)a.m;
+    if (a.n_out == 1)
+        k_predict_ksum<1><<<rows, 128, 0, s>>>(a, kbuf, kst);
+    else if (a.n_out <= 4)
+        k_predict_ksum<4><<<rows, 128, 0, s>>>(a, kbuf, kst);
+    else
+        k_predict_ksum<16><<<rows, 128, 0, s>>>(a, kbuf, kst);
 }
 
 }  // namespace msvm

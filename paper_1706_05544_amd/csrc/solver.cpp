@@ -1,5 +1,6 @@
 // Host side of the working-set dual solve: buffers, the iteration loop,
 // the final recompute of the responses, bias, objective and the model.
+#include "predict.hpp"
 #include "solver.hpp"
 
 #include "resident.hpp"
@@ -2170,6 +2171,16 @@ void predict_rows(PredictArgs a, const Features& t, hipStream_t s,
         a.sqt = t.sq.p;
         a.m = t.n;
         a.row_base = 0;
+        // (a buffer of more than 2 MB takes 50 us to allocate and free, more
+        // than the two kernels gain on rows of up to 128 features: 300 x 128
+        // against 6600 support rows 133 -> 153 us)
+        const int64_t few = predict_few_floats(a.nsv, t.n, t.ldp);
+        if (few > 0 && (few <= (int64_t)1 << 19 || t.ldp > 128)) {
+            DevBuf<float> kbuf((size_t)few);
+            launch_predict_few(a, kbuf.p, s);
+            HIP_TRY(hipStreamSynchronize(s));
+            return;
+        }
         DevBuf<double> part;
         if (a.nrange > 1 && t.n > 0) {
             part.alloc((size_t)predict_part_doubles(a.nsv, t.n, a.n_out));

@@ -1,0 +1,67 @@
+"""Decision values of few query rows and of wide rows against large batches.
+
+The batch a row comes in chooses the path (few rows: kernel values of all
+tiles at once, then the sums; many: one kernel), never the bits: rows of a
+small call must equal, bit for bit, the same rows inside a batch of the
+one-kernel path, and both the oracle.  Sizes around the tiles of both paths
+(16, 64 and 128 rows; 16-, 32- and 64-feature chunks; one and several ranges
+of support rows, whole and ragged) and of their rules.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1706_05544_amd import native as nv
+
+RBF, SIG = nv.SVM_KERNEL_RBF, nv.SVM_KERNEL_SIGMOID
+pytestmark = pytest.mark.gpu
+
+
+def _model(nsv, d, kernel, n_out):
+    rng = np.random.default_rng(nsv * 1009 + d)
+    X = rng.standard_normal((nsv, d), dtype=np.float32)
+    kw = dict(kernel=kernel, gamma=1.0 / d, C=1.0, tol=1e6)
+    if n_out > 1:
+        y = (np.arange(nsv) % n_out).astype(np.float32)
+        return X, nv.svm_train_ovr(X, y, n_out, kernel=kernel, gamma=1.0 / d,
+                                   max_iter=60)
+    y = np.where(np.arange(nsv) % 2 == 0, 1.0, -1.0).astype(np.float32)
+    alpha = np.full(nsv, 0.5)  # every row a support row, y^T alpha = 0
+    if nsv % 2:
+        alpha[[-3, -1]] = 0.25
+    return X, nv.svm_train(X, y, alpha0=alpha, **kw)
+
+
+@pytest.mark.parametrize("nsv,d,kernel,n_out", [
+    (700, 20, RBF, 1),       # one range, just past the tile-work rule
+    (1601, 128, RBF, 1),     # two ranges, the last tile one row
+    (3007, 129, RBF, 1),     # wide rows, a ragged chunk
+    (1000, 160, SIG, 1),     # another kernel
+    (12801, 131, RBF, 1),    # eight ranges
+    (257, 784, RBF, 1),      # odd half step of 128 support rows
+    (900, 130, RBF, 3),
+    (1700, 40, RBF, 10),
+])
+def test_batch_does_not_change_the_bits(nsv, d, kernel, n_out):
+    X, model = _model(nsv, d, kernel, n_out)
+    rng = np.random.default_rng(d)
+    big = 128 * 64 + 77
+    Xt = torch.from_numpy(rng.standard_normal((big, d), dtype=np.float32))
+    Xd = Xt.to("cuda:0")
+    D = nv.svm_predict(model, Xd).reshape(big, -1)
+    for m in (1, 15, 17, 64, 65, 300, 1111, 2049):
+        Dm = nv.svm_predict(model, Xd[:m].contiguous()).reshape(m, -1)
+        assert torch.equal(Dm, D[:m]), m
+        out = torch.full((m, n_out), float("nan"), dtype=torch.float64,
+                         device="cuda:0")
+        nv.svm_predict_noalloc(model, Xd[:m].contiguous(), out)
+        assert torch.equal(out, D[:m]), m
+    if n_out == 1 and kernel == RBF:
+        idx, cf, _ = nv.svm_model_get(model, 0)
+        ref = oracle.decision(X[idx], cf, model.info()["b"],
+                              Xt[:200].numpy(), 1.0 / d)
+        # fp32 kernel values (d products, one exponential) against fp64
+        tol = np.abs(cf).sum() * (d + 40) * 2.0 ** -24
+        np.testing.assert_allclose(D[:200, 0].cpu().numpy(), ref, rtol=0,
+                                   atol=tol)
