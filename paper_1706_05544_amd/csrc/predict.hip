@@ -356,6 +356,254 @@ __global__ __launch_bounds__(256) void k_predict_ra4(PredictArgs a)
     predict_ra_body<4>(a);
 }
 
+// ---------------------------------------------------------------------------
+// wide rows
+// ---------------------------------------------------------------------------
+//
+// Rows of more than kRaMaxLdp features, one output.  Matrix-core work bounds
+// this, so the tile is as large as the registers allow at two waves a SIMD:
+// a block of four waves takes 128 query rows (32 a wave, straight from
+// memory into the operand layout) against 128 support rows a step, staged in
+// LDS by chunks of 32 features, double-buffered, one barrier a chunk; half
+// the operand traffic per product of k_predict's 64 x 64 tiles and a fourth
+// of its barriers.  The 32x32x2 instruction adds its products one by one in
+// feature order, as 16x16x4 does, so two of them give the same bits as one
+// step of mfma_chunk, at half the instructions.
+//
+// 50001 x 783 against 12002 support rows (MI355X): 10.2 ms with k_predict,
+// 8.4 ms here (112 TFLOP/s; a loop of this instruction alone sustains 138 to
+// 147): 12.2 blocks a compute unit, so the last ones run alone, and 5 in 100
+// for the values and sums at the end of a step.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+constexpr int kWideRows = 128;    // query rows and support rows of a step
+constexpr int kWideDK = 32;       // features a chunk
+constexpr int kWideSlots = kWideRows * kWideDK / 4;  // float4 of a chunk
+
+__global__ __launch_bounds__(256, 2) void k_predict_wide(PredictArgs a)
+{
+    __shared__ __align__(16) float4 Bs[2][kWideSlots];
+    __shared__ __align__(16) double Cs[kWideRows];
+    __shared__ float Qs[kWideRows];
+    __shared__ int32_t Ts[kWideRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 31, hf = lane >> 5;  // operand row, float4 of a pair
+    const int nl = lane & 15, odd = (lane >> 4) & 1;
+    const int ldp = (int)a.ldp;
+    const int64_t m = a.m, nsv = a.nsv;
+    // consecutive blocks run on different dies: the ranges of a group of
+    // query rows go to one of them, where they read the same rows at about
+    // the same time
+    const int64_t b = blockIdx.x;
+    const int64_t nq = (m + kWideRows - 1) / kWideRows;
+    const int64_t t8 = b / 8;
+    const int64_t qb = t8 / a.nrange * 8 + b % 8;
+    const int range = (int)(t8 % a.nrange);
+    if (qb >= nq) return;
+    const int64_t row0 = qb * kWideRows + 32 * wave;  // this wave's 32 rows
+    int64_t sv_lo, sv_hi;
+    predict_range_of(nsv, a.nrange, range, sv_lo, sv_hi);
+    const int nch = (ldp + kWideDK - 1) / kWideDK;
+
+    const Rsrc rA = make_rsrc(
+        a.Xt + (row0 < m ? row0 : 0) * ldp,
+        row0 < m ? min((int64_t)32, m - row0) * ldp * 4 : 0);
+    float4 av[2][4];  // [buffer][pair of float4 of the chunk]
+    auto fetchA = [&](int c, float4 (&x)[4]) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int col = kWideDK * c + 8 * p + 4 * hf;
+            x[p] = bld_f4(rA, col < ldp ? (uint32_t)((ln * ldp + col) * 4)
+                                        : kOob);
+        }
+    };
+    // A support chunk: 128 rows x 8 float4, row r's float4 f in slot 8 r +
+    // (f ^ (r / 2 & 7)): the 16 rows that a matrix-core operand reads at one
+    // f lie in 16 different groups of four banks.  Thread t moves the slots
+    // t, t + 256, ..: row t / 8 + 32 k.
+    const int lr = tid >> 3, lf = (tid & 7) ^ ((lr >> 1) & 7);
+    float4 bp[4];
+    auto fetchB = [&](int64_t s0, int c) {
+        const Rsrc rB = make_rsrc(
+            a.SV + s0 * ldp,
+            min((int64_t)kWideRows, sv_hi - s0) * ldp * 4);
+        const int col = kWideDK * c + 4 * lf;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            bp[k] = bld_f4(rB, col < ldp
+                                   ? (uint32_t)(((lr + 32 * k) * ldp + col) * 4)
+                                   : kOob);
+    };
+    auto putB = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Bs[buf][tid + 256 * k] = bp[k];
+    };
+
+    double part[8];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) part[v] = 0.0;
+    floatx16 acc[4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[cb][v] = 0.0f;
+
+    int64_t s0 = sv_lo;   // the step, and chunk of it, being computed
+    int c = 0;
+    int64_t ns0 = sv_lo;  // of the support chunk being fetched
+    int nc = 0;
+    auto advance = [&](int64_t& s, int& k) {
+        if (++k == nch) {
+            k = 0;
+            s += kWideRows;
+        }
+    };
+    if (s0 < sv_hi) {
+        fetchB(ns0, nc);
+        fetchA(0, av[0]);
+        putB(0);
+        advance(ns0, nc);
+        if (ns0 < sv_hi) fetchB(ns0, nc);
+    }
+    __syncthreads();
+
+    auto chunk = [&](int buf, const float4 (&x)[4]) {
+        // a half's LDS reads all before its products (left to itself the
+        // compiler reads each operand just before its use, and a product
+        // waits for LDS every 16 instructions)
+        float4 y[4][4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                const int r = 32 * cb + ln;
+                y[p][cb] = Bs[buf][8 * r + ((2 * p + hf) ^ ((r >> 1) & 7))];
+            }
+            if (p & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (kWideDK * c + 16 * h >= ldp) break;  // uniform
+            // mfma_chunk's order in each tile (component by component, the
+            // four float4 in order), the tiles side by side
+            auto feature = [&](auto of) {
+#pragma unroll
+                for (int p = 2 * h; p < 2 * h + 2; ++p)
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb)
+                        acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                            of(x[p]), of(y[p][cb]), acc[cb], 0, 0, 0);
+            };
+            feature([](const float4& q) { return q.x; });
+            feature([](const float4& q) { return q.y; });
+            feature([](const float4& q) { return q.z; });
+            feature([](const float4& q) { return q.w; });
+        }
+    };
+    // row of the wave's 32 that this lane keeps the sums of, v = 0 .. 7
+    auto row_of = [&](int v) {
+        return (v & 3) + 8 * (v >> 2) + 4 * hf + 16 * odd;
+    };
+    auto epilogue = [&]() {
+        float sqr[8];
+        int32_t rself[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const int64_t r = row0 + row_of(v);
+            sqr[v] = r < m ? a.sqt[r] : 0.0f;
+            rself[v] = (int32_t)(r + a.row_base);
+        }
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            // a lane has one column of 32 and 16 rows; the 16-lane rows of
+            // the wave exchange halves so that it has columns nl and 16 + nl
+            // and 8 rows: the sums of the other kernels, lane by lane
+            const int j0 = 32 * cb + nl, j1 = j0 + 16;
+            float k0[8], k1[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                const auto e = __builtin_amdgcn_permlane16_swap(
+                    (unsigned)__float_as_int(acc[cb][v]),
+                    (unsigned)__float_as_int(acc[cb][v + 8]), false, false);
+                k0[v] = __int_as_float((int)e[0]);
+                k1[v] = __int_as_float((int)e[1]);
+                acc[cb][v] = 0.0f;
+                acc[cb][v + 8] = 0.0f;
+            }
+            const float ss0 = Qs[j0], ss1 = Qs[j1];
+            const int32_t t0 = Ts[j0], t1 = Ts[j1];
+            if (a.kf.kind == SVM_KERNEL_RBF) {
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    k0[v] = rbf_from_dot(sqr[v], ss0, k0[v], a.kf.gexp);
+                    k1[v] = rbf_from_dot(sqr[v], ss1, k1[v], a.kf.gexp);
+                    if (t0 == rself[v]) k0[v] = 1.0f;
+                    if (t1 == rself[v]) k1[v] = 1.0f;
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    k0[v] = kernel_of_dot(a.kf, k0[v]);
+                    k1[v] = kernel_of_dot(a.kf, k1[v]);
+                }
+            }
+            const double c0 = Cs[j0], c1 = Cs[j1];
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+                part[v] = fma(c1, (double)k1[v],
+                              fma(c0, (double)k0[v], part[v]));
+        }
+    };
+
+    // One barrier a chunk: while chunk p is multiplied, p + 1 goes from
+    // registers into the other buffer (read last before the barrier at the
+    // end of p - 1) and p + 2 is requested.
+    float eq = 0.0f;
+    int32_t et = -1;
+    double ec = 0.0;
+    auto body = [&](int buf, const float4 (&x)[4], float4 (&xn)[4]) {
+        if (c == 0 && tid < kWideRows) {  // the step's epilogue data
+            const int64_t j = s0 + tid;
+            const bool ok = j < sv_hi;
+            eq = ok ? a.sqsv[j] : 0.0f;
+            et = (ok && a.self_match) ? a.sv_train_idx[j] : -1;
+            ec = ok ? a.coef[j] : 0.0;
+        }
+        if (ns0 < sv_hi) putB(buf ^ 1);
+        advance(ns0, nc);
+        if (ns0 < sv_hi) fetchB(ns0, nc);
+        fetchA(c + 1 == nch ? 0 : c + 1, xn);
+        if (c == nch - 2 && tid < kWideRows) {
+            Qs[tid] = eq;
+            Ts[tid] = et;
+            Cs[tid] = ec;
+        }
+        chunk(buf, x);
+        __syncthreads();
+        if (c == nch - 1) epilogue();
+        advance(s0, c);
+    };
+    while (s0 < sv_hi) {
+        body(0, av[0], av[1]);
+        if (s0 >= sv_hi) break;
+        body(1, av[1], av[0]);
+    }
+
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        double p = part[v];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) p += __shfl_xor(p, off, 16);
+        const int64_t row = row0 + row_of(v);
+        if (nl == v && row < m) {
+            if (a.nrange <= 1)
+                a.out[row] = p + (a.b ? a.b[0] : 0.0);
+            else
+                a.part[(int64_t)range * m + row] = p;
+        }
+    }
+}
+
 // out = the ranges' partial sums added in range order, + b
 __global__ void k_predict_sum(const double* part, int nrange, int64_t mn,
                               int n_out, const double* b, double* out)
@@ -393,8 +641,10 @@ void launch_predict(const PredictArgs& a, hipStream_t s)
             k_predict_ra1<<<grid, 256, 0, s>>>(a);
         else
             k_predict_ra4<<<grid, 256, 0, s>>>(a);
-    } else if (a.n_out <= 1) {
-        k_predict<1><<<grid, 256, 0, s>>>(a);
+    } else if (a.n_out <= 1 && a.ldp > kRaMaxLdp && a.ldp <= kFewMaxLdp) {
+        const int64_t nq = (a.m + kWideRows - 1) / kWideRows;
+        k_predict_wide<<<(unsigned)((nq + 7) / 8 * 8 * a.nrange), 256, 0,
+                         s>>>(a);
     } else if (a.n_out <= 4) {
         k_predict<4><<<grid, 256, 0, s>>>(a);
     } else if (a.n_out <= 16) {
