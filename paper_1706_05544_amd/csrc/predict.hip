@@ -630,6 +630,16 @@ int64_t predict_part_doubles(int64_t nsv, int64_t m, int32_t n_out)
     return r > 1 ? (int64_t)r * m * n_out : 0;
 }
 
+static void launch_predict_sum(const PredictArgs& a, hipStream_t s)
+{
+    if (a.nrange <= 1) return;
+    const int64_t mn = a.m * a.n_out;
+    const unsigned blocks =
+        (unsigned)std::min<int64_t>((mn + 255) / 256, 4096);
+    k_predict_sum<<<blocks, 256, 0, s>>>(a.part, a.nrange, mn, a.n_out, a.b,
+                                         a.out);
+}
+
 void launch_predict(const PredictArgs& a, hipStream_t s)
 {
     if (a.m <= 0) return;
@@ -652,13 +662,7 @@ void launch_predict(const PredictArgs& a, hipStream_t s)
     } else {
         throw Error{SVM_E_UNSUPPORTED, "more than 16 outputs"};
     }
-    if (a.nrange > 1) {
-        const int64_t mn = a.m * a.n_out;
-        const unsigned blocks =
-            (unsigned)std::min<int64_t>((mn + 255) / 256, 4096);
-        k_predict_sum<<<blocks, 256, 0, s>>>(a.part, a.nrange, mn, a.n_out,
-                                             a.b, a.out);
-    }
+    launch_predict_sum(a, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -894,8 +898,11 @@ namespace msvm {
 // product with a zero.  The support rows are grouped in chunks of 16 and
 // stored by column (the columns some row of the chunk holds, increasing,
 // each with the 16 values).  A block owns 256 query rows, one per lane, with
-// the first kSpRegNz nonzeros of each in registers, and walks over all
-// chunks: while it sums chunk k it writes chunk k + 1 into LDS (a map
+// the first kSpRegNz nonzeros of each in registers, and walks over the
+// chunks of one range of support rows (the ranges of the dense paths, added
+// in range order by k_predict_sum: 100000 rows are 391 blocks, which left a
+// fourth of the chip idle, 1000 rows 4 blocks; 100000 x 1000, 20 nonzeros a
+// row, against 20000 support rows 6.01 -> 5.19 ms): while it sums chunk k it writes chunk k + 1 into LDS (a map
 // column -> (chunk, table row), the table, the chunk's norms and
 // coefficients) from registers and loads chunk k + 2 into them, one barrier
 // per chunk.  Per query nonzero at column c the lane looks c up
@@ -942,7 +949,10 @@ __global__ __launch_bounds__(kSpThreads) void k_predict_sparse(PredictArgs a)
     const int tid = threadIdx.x;
     const int64_t ldp = a.ldp, nsv = a.nsv;
     const int cap = a.ch_cap, n_out = a.n_out;
-    const int64_t nchunk = (nsv + 15) / 16;
+    // this block's range of support rows, in chunks
+    int64_t sv_lo, sv_hi;
+    predict_range_of(nsv, a.nrange, (int)blockIdx.y, sv_lo, sv_hi);
+    const int64_t klo = sv_lo / 16, khi = (sv_hi + 15) / 16;
     const size_t per = sp_buf_bytes(ldp, cap);
     auto map_of = [&](int p) {
         return reinterpret_cast<int2*>(smem + p * per);
@@ -1029,11 +1039,11 @@ __global__ __launch_bounds__(kSpThreads) void k_predict_sparse(PredictArgs a)
         if (tid < 16 * NOUT) coef_of(p)[tid] = q.cf;
     };
     Pre pre;
-    if (nchunk > 0) {
-        fetch(0, pre);
-        put(0, 0, pre);
+    if (klo < khi) {
+        fetch(klo, pre);
+        put(klo, (int)(klo & 1), pre);
     }
-    if (nchunk > 1) fetch(1, pre);
+    if (klo + 1 < khi) fetch(klo + 1, pre);
 
     // this lane's query row
     const int64_t r = (int64_t)blockIdx.x * kSpThreads + tid;
@@ -1059,15 +1069,15 @@ __global__ __launch_bounds__(kSpThreads) void k_predict_sparse(PredictArgs a)
     double outv[NOUT];
 #pragma unroll
     for (int o = 0; o < NOUT; ++o) outv[o] = 0.0;
-    // the query nonzeros (and chunk 1) have arrived: no wait on them inside
+    // the query nonzeros (and the second chunk) have arrived: no wait on them inside
     // the chunk loop
     __builtin_amdgcn_s_waitcnt(kVmcnt0);
     __syncthreads();
 
-    for (int64_t k = 0; k < nchunk; ++k) {
+    for (int64_t k = klo; k < khi; ++k) {
         const int p = (int)(k & 1);
-        if (k + 1 < nchunk) put(k + 1, p ^ 1, pre);
-        if (k + 2 < nchunk) fetch(k + 2, pre);
+        if (k + 1 < khi) put(k + 1, p ^ 1, pre);
+        if (k + 2 < khi) fetch(k + 2, pre);
         const int2* mp = map_of(p);
         const float* tb = tab_of(p);
         float acc[16];
@@ -1145,8 +1155,13 @@ __global__ __launch_bounds__(kSpThreads) void k_predict_sparse(PredictArgs a)
     if (rv) {
 #pragma unroll
         for (int o = 0; o < NOUT; ++o)
-            if (o < n_out)
-                a.out[r * n_out + o] = outv[o] + (a.b ? a.b[o] : 0.0);
+            if (o < n_out) {
+                if (a.nrange <= 1)
+                    a.out[r * n_out + o] = outv[o] + (a.b ? a.b[o] : 0.0);
+                else
+                    a.part[((int64_t)blockIdx.y * a.m + r) * n_out + o] =
+                        outv[o];
+            }
     }
 }
 
@@ -1155,7 +1170,10 @@ void launch_predict_sparse(const PredictArgs& a, hipStream_t s)
     if (a.m <= 0) return;
     if (!predict_sparse_fits(a.ldp, a.ch_cap))
         throw Error{SVM_E_INTERNAL, "sparse decision tables exceed LDS"};
-    const unsigned blocks = (unsigned)((a.m + kSpThreads - 1) / kSpThreads);
+    if (a.nrange < 1 || a.nrange > 8 || (a.nrange > 1 && !a.part))
+        throw Error{SVM_E_INTERNAL, "decision ranges"};
+    const dim3 blocks((unsigned)((a.m + kSpThreads - 1) / kSpThreads),
+                      (unsigned)a.nrange);
     const size_t lds = predict_sparse_lds_bytes(a.ldp, a.ch_cap);
     if (a.n_out <= 1)
         k_predict_sparse<1><<<blocks, kSpThreads, lds, s>>>(a);
@@ -1165,6 +1183,7 @@ void launch_predict_sparse(const PredictArgs& a, hipStream_t s)
         k_predict_sparse<16><<<blocks, kSpThreads, lds, s>>>(a);
     else
         throw Error{SVM_E_UNSUPPORTED, "more than 16 outputs"};
+    launch_predict_sum(a, s);
 }
 
 // One block per chunk of 16 support rows: flag the columns the rows hold,

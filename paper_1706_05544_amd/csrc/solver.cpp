@@ -2222,13 +2222,29 @@ void predict_rows(PredictArgs a, const Features& t, hipStream_t s,
         return;
     }
     if (a.ch_tab && t.nnz <= 32 * t.n) {
-        a.rpt = t.rp.p;
         a.cit = t.ci.p;
         a.cvt = t.cv.p;
-        a.sqt = t.sq.p;
-        a.m = t.n;
-        a.row_base = 0;
-        launch_predict_sparse(a, s);
+        // slabs of whole blocks of rows whose partial sums stay below 128 MB
+        const int64_t per = (int64_t)a.nrange * a.n_out * 8;
+        const int64_t slab =
+            a.nrange > 1 ? std::min(t.n, (((int64_t)128 << 20) / per) &
+                                             ~(int64_t)255)
+                         : t.n;
+        DevBuf<double> part;
+        if (a.nrange > 1 && t.n > 0) {
+            part.alloc((size_t)predict_part_doubles(a.nsv, slab, a.n_out));
+            a.part = part.p;
+        }
+        double* out0 = a.out;
+        for (int64_t r0 = 0; r0 < t.n; r0 += slab) {
+            a.rpt = t.rp.p + r0;
+            a.sqt = t.sq.p + r0;
+            a.m = std::min(slab, t.n - r0);
+            a.row_base = r0;
+            a.out = out0 + r0 * a.n_out;
+            launch_predict_sparse(a, s);
+        }
+        if (part.p) HIP_TRY(hipStreamSynchronize(s));
         return;
     }
     if (!a.SV)

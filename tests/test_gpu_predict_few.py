@@ -5,10 +5,12 @@ tiles at once, then the sums; many: one kernel), never the bits: rows of a
 small call must equal, bit for bit, the same rows inside a batch of the
 one-kernel path, and both the oracle.  Sizes around the tiles of both paths
 (16, 64 and 128 rows; 16-, 32- and 64-feature chunks; one and several ranges
-of support rows, whole and ragged) and of their rules.
+of support rows, whole and ragged) and of their rules.  Sparse rows: the table
+path over ranges of support rows and slabs of query rows.
 """
 import numpy as np
 import pytest
+import scipy.sparse as sp
 import torch
 
 import oracle
@@ -65,3 +67,44 @@ def test_batch_does_not_change_the_bits(nsv, d, kernel, n_out):
         tol = np.abs(cf).sum() * (d + 40) * 2.0 ** -24
         np.testing.assert_allclose(D[:200, 0].cpu().numpy(), ref, rtol=0,
                                    atol=tol)
+
+
+def _csr(n, d, nnz, seed):
+    rng = np.random.default_rng(seed)
+    cols = (np.arange(n)[:, None] * 7 + np.cumsum(
+        rng.integers(1, d // nnz, (n, nnz)), axis=1)) % d
+    cols.sort(axis=1)
+    vals = rng.standard_normal((n, nnz), dtype=np.float32)
+    return sp.csr_matrix((vals.ravel(), cols.ravel().astype(np.int32),
+                          np.arange(n + 1) * nnz), shape=(n, d))
+
+
+@pytest.mark.parametrize("nsv,n_out,m", [
+    (1500, 1, 700),        # one range
+    (1601, 1, 5001),       # two, the last chunk one row
+    (13003, 1, 3000),      # eight
+    (9000, 10, 300001),    # more rows than one slab of partial sums
+])
+def test_sparse_ranges(nsv, n_out, m):
+    # 20 of 1000 columns a row: the table path in every batch size
+    X = _csr(nsv, 1000, 20, 1)
+    if n_out > 1:
+        y = (np.arange(nsv) % n_out).astype(np.float32)
+        model = nv.svm_train_ovr(X, y, n_out, gamma=0.05, max_iter=50)
+    else:
+        y = np.where(np.arange(nsv) % 2 == 0, 1.0, -1.0).astype(np.float32)
+        alpha = np.full(nsv, 0.5)
+        if nsv % 2:
+            alpha[[-3, -1]] = 0.25
+        model = nv.svm_train(X, y, gamma=0.05, alpha0=alpha, tol=1e6)
+    Xt = _csr(m, 1000, 20, 2)
+    D = nv.svm_predict(model, Xt).reshape(m, -1)
+    for a, b in ((0, 1), (0, 257), (m - 300, m)):
+        np.testing.assert_array_equal(
+            nv.svm_predict(model, Xt[a:b]).reshape(b - a, -1), D[a:b])
+    idx, cf, _ = nv.svm_model_get(model, 0)
+    SV = oracle.Matrix(X).rows(idx)
+    ref = oracle.decision(SV, cf, model.info(0)["b"], Xt[-300:], 0.05)
+    # fp32 kernel values (20 products, one exponential) against fp64
+    np.testing.assert_allclose(D[-300:, 0], ref, rtol=0,
+                               atol=np.abs(cf).sum() * 60 * 2.0 ** -24)
