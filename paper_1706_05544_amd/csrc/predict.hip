@@ -360,7 +360,11 @@ __global__ __launch_bounds__(256) void k_predict_ra4(PredictArgs a)
 // wide rows
 // ---------------------------------------------------------------------------
 //
-// Rows of more than kRaMaxLdp features, one output.  Matrix-core work bounds
+// Rows of more than kRaMaxLdp features, one output (at 128 features the
+// values and sums at the end of a step weigh too much for two waves a SIMD:
+// 20000 x 128 against 6600 support rows 389 us with k_predict_ra1, 456 here;
+// 129 features, 50001 against 3000, 631 with k_predict, 569 here).
+// Matrix-core work bounds
 // this, so the tile is as large as the registers allow at two waves a SIMD:
 // a block of four waves takes 128 query rows (32 a wave, straight from
 // memory into the operand layout) against 128 support rows a step, staged in
@@ -902,16 +906,17 @@ namespace msvm {
 // chunks of one range of support rows (the ranges of the dense paths, added
 // in range order by k_predict_sum: 100000 rows are 391 blocks, which left a
 // fourth of the chip idle, 1000 rows 4 blocks; 100000 x 1000, 20 nonzeros a
-// row, against 20000 support rows 6.01 -> 5.19 ms): while it sums chunk k it writes chunk k + 1 into LDS (a map
-// column -> (chunk, table row), the table, the chunk's norms and
-// coefficients) from registers and loads chunk k + 2 into them, one barrier
-// per chunk.  Per query nonzero at column c the lane looks c up
-// and, if the chunk holds it, adds v * x_s[c] to its 16 dot products: the
-// sum over the common nonzeros in the query row's column order, as every
-// CSR kernel of the library sums it (the skipped products are products with
-// a zero, which change nothing), so the K values are bitwise those of the
-// training kernels.  Per output, c_s K is accumulated in fp64 in chunk and
-// slot order: no atomics, the result does not depend on scheduling.
+// row, against 20000 support rows 6.01 -> 5.19 ms): while it sums chunk k it
+// writes chunk k + 1 into LDS (a map column -> (chunk, table row), the
+// table, the chunk's norms and coefficients) from registers and loads chunk
+// k + 2 into them, one barrier per chunk.  Per query nonzero at column c the
+// lane looks c up and, if the chunk holds it, adds v * x_s[c] to its 16 dot
+// products: the sum over the common nonzeros in the query row's column
+// order, as every CSR kernel of the library sums it (the skipped products
+// are products with a zero, which change nothing), so the K values are
+// bitwise those of the training kernels.  Per output, c_s K is accumulated
+// in fp64 in chunk and slot order: no atomics, the result does not depend on
+// scheduling.
 
 constexpr int kSpThreads = 256;
 constexpr int kSpRegNz = 32;  // query nonzeros held in registers
