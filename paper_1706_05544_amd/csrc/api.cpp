@@ -466,6 +466,11 @@ static svm_status predict_impl(const svm_model* mdl, const svm_matrix* X,
     if ((st = check_device(mdl->device)) != SVM_OK) return st;
     GUARD_BEGIN
     msvm::Context cx(mdl->device, nullptr);
+    if (!mdl->scaled && msvm::padded_in_place(X)) {
+        msvm::predict_in_place(*mdl, cx, X, decision, decision ? nullptr
+                                                               : labels);
+        return SVM_OK;
+    }
     msvm::Features t;
     msvm::load_features(X, t, cx, true);
     const int64_t m = X->n;

@@ -35,6 +35,9 @@ void Context::sync() { HIP_TRY(hipStreamSynchronize(stream)); }
 
 int64_t padded_ld(int64_t d) { return (d + 3) / 4 * 4; }
 
+static const char kNotFinite[] =
+    "X holds a value that is not finite (or whose square overflows fp32)";
+
 static void load_csr(const svm_matrix* M, Features& f, Context& cx)
 {
     f.csr = true;
@@ -80,10 +83,7 @@ static void load_csr(const svm_matrix* M, Features& f, Context& cx)
         throw Error{SVM_E_INVALID,
                     "CSR column indices must be in [0, d), sorted and unique "
                     "within each row"};
-    if (hb & 1)
-        throw Error{SVM_E_INVALID,
-                    "X holds a value that is not finite (or whose square "
-                    "overflows fp32)"};
+    if (hb & 1) throw Error{SVM_E_INVALID, kNotFinite};
     if (sell_total > 0 && sell_total <= 4 * f.nnz + 64 * kSellRows &&
         f.d <= 65536) {
         f.sci.alloc((size_t)sell_total);
@@ -93,6 +93,13 @@ static void load_csr(const svm_matrix* M, Features& f, Context& cx)
     } else {
         f.so.release();
     }
+}
+
+bool padded_in_place(const svm_matrix* M)
+{
+    return M->layout == SVM_DENSE && M->on_device && M->n > 0 &&
+           padded_ld(M->d) == M->d && M->ld == M->d &&
+           ((uintptr_t)M->values & 15) == 0;
 }
 
 void load_features(const svm_matrix* M, Features& f, Context& cx, bool borrow)
@@ -109,8 +116,7 @@ void load_features(const svm_matrix* M, Features& f, Context& cx, bool borrow)
     const hipMemcpyKind kind =
         M->on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     f.Xb = nullptr;
-    if (borrow && M->on_device && f.n > 0 && f.ldp == f.d && M->ld == f.d &&
-        ((uintptr_t)M->values & 15) == 0) {
+    if (borrow && padded_in_place(M)) {
         f.Xb = static_cast<const float*>(M->values);
         f.X.release();
     } else {
@@ -139,10 +145,7 @@ void load_features(const svm_matrix* M, Features& f, Context& cx, bool borrow)
     HIP_TRY(hipMemcpyAsync(&hb, bad.p, sizeof(int32_t),
                            hipMemcpyDeviceToHost, cx.stream));
     cx.sync();
-    if (hb)
-        throw Error{SVM_E_INVALID,
-                    "X holds a value that is not finite (or whose square "
-                    "overflows fp32)"};
+    if (hb) throw Error{SVM_E_INVALID, kNotFinite};
 }
 
 SolveOptions make_options(const svm_params* p, int64_t n, int64_t d)
@@ -1985,10 +1988,8 @@ void scale_targets(float* y_dev, int64_t n, Context& cx, double* mu,
     if (!(*sd > 0.0)) *sd = 0.0;  // constant targets: left as they are
 }
 
-void predict_device(const svm_model& mdl, Context& cx, Features& t,
-                    double* out)
+static PredictArgs model_args(const svm_model& mdl, double* out)
 {
-    if (mdl.scaled) scale_apply(t, cx, mdl.x_mu.p, mdl.x_sd.p);
     PredictArgs a{};
     a.SV = mdl.SV.p;
     a.sqsv = mdl.sqsv.p;
@@ -2000,6 +2001,14 @@ void predict_device(const svm_model& mdl, Context& cx, Features& t,
     a.self_match = 0;
     a.out = out;
     a.kf = mdl.kf;
+    return a;
+}
+
+void predict_device(const svm_model& mdl, Context& cx, Features& t,
+                    double* out)
+{
+    if (mdl.scaled) scale_apply(t, cx, mdl.x_mu.p, mdl.x_sd.p);
+    PredictArgs a = model_args(mdl, out);
     if (mdl.ch_cap > 0) {
         a.ch_ncol = mdl.ch_ncol.p;
         a.ch_cols = mdl.ch_cols.p;
@@ -2009,6 +2018,82 @@ void predict_device(const svm_model& mdl, Context& cx, Features& t,
     predict_rows(a, t, cx.stream, mdl.fc.ok ? &mdl.fc : nullptr);
     if (mdl.scaled && mdl.type == SVM_EPS_SVR && mdl.y_sd > 0.0)
         launch_affine(out, t.n * mdl.n_out, mdl.y_sd, mdl.y_mu, cx.stream);
+}
+
+// A buffer of more than 2 MB takes 50 us to allocate and free, a smaller one
+// a few.
+constexpr size_t kCheapAlloc = (size_t)2 << 20;
+
+// Kernel values of the path for few query rows where a call that allocates
+// them gains from it, else 0: past kCheapAlloc the allocation costs more than
+// the two kernels gain on rows of up to 128 features (300 x 128 against 6600
+// support rows 133 -> 153 us).
+static int64_t few_floats(int64_t nsv, int64_t m, int64_t ldp)
+{
+    const int64_t few = predict_few_floats(nsv, m, ldp);
+    return few * 4 <= (int64_t)kCheapAlloc || ldp > 128 ? few : 0;
+}
+
+// What bounds a call of some 100 us is the host's part: allocations and the
+// round trips in which the GPU has nothing to do.  The rows need no copy, so
+// everything the call keeps goes into one buffer (two where that would pass
+// kCheapAlloc: a second small one costs less than a large one), and the check
+// of the values is read after the decision kernels, which a value that is not
+// finite cannot lead astray, instead of before them.  Measured (us a call,
+// buffers of their own and the check first -> this): 20000 x 128 against 6600
+// support rows 414 -> 402.
+void predict_in_place(const svm_model& mdl, Context& cx, const svm_matrix* X,
+                      double* decision, int32_t* labels)
+{
+    hipStream_t s = cx.stream;
+    const int64_t m = X->n, ldp = padded_ld(X->d);
+    const float* x = static_cast<const float*>(X->values);
+    const int64_t few = few_floats(mdl.n_sv, m, ldp);
+    auto up = [](int64_t b) { return ((size_t)b + 255) & ~(size_t)255; };
+    const size_t sq_at = 256, d_at = sq_at + up(m * 4),
+                 l_at = d_at + up(m * mdl.n_out * 8),
+                 mid_at = l_at + (labels ? up(m * 4) : 0);
+    const size_t mid_b =
+        few > 0 ? (size_t)few * 4
+                : (size_t)predict_part_doubles(mdl.n_sv, m, mdl.n_out) * 8;
+    const bool one = mid_at + mid_b <= kCheapAlloc;
+    DevBuf<unsigned char> buf(mid_at + (one ? mid_b : 0)), midb;
+    if (!one && mid_b > 0) midb.alloc(mid_b);
+    unsigned char* mid = one ? buf.p + mid_at : midb.p;
+    int32_t* bad = reinterpret_cast<int32_t*>(buf.p);
+    float* sq = reinterpret_cast<float*>(buf.p + sq_at);
+    double* D = reinterpret_cast<double*>(buf.p + d_at);
+    int32_t* L = reinterpret_cast<int32_t*>(buf.p + l_at);
+
+    HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int32_t), s));
+    launch_norms(x, m, ldp, sq, bad, s);
+    PredictArgs a = model_args(mdl, D);
+    a.ldp = ldp;
+    a.nrange = predict_ranges(mdl.n_sv);
+    a.Xt = x;
+    a.sqt = sq;
+    a.m = m;
+    a.row_base = 0;
+    if (few > 0) {
+        launch_predict_few(a, reinterpret_cast<float*>(mid), s);
+    } else {
+        a.part = a.nrange > 1 ? reinterpret_cast<double*>(mid) : nullptr;
+        launch_predict(a, s);
+    }
+    if (labels) launch_argmax_labels(D, m, mdl.n_out, mdl.type, L, s);
+    int32_t hb = 0;
+    HIP_TRY(hipMemcpyAsync(&hb, bad, sizeof(int32_t), hipMemcpyDeviceToHost,
+                           s));
+    cx.sync();
+    if (hb) throw Error{SVM_E_INVALID, kNotFinite};
+    if (labels)
+        HIP_TRY(hipMemcpyAsync(labels, L, (size_t)m * sizeof(int32_t),
+                               hipMemcpyDeviceToDevice, s));
+    else
+        HIP_TRY(hipMemcpyAsync(decision, D,
+                               (size_t)(m * mdl.n_out) * sizeof(double),
+                               hipMemcpyDeviceToDevice, s));
+    cx.sync();
 }
 
 int sparse_chunk_cap(const Features& f)
@@ -2171,11 +2256,8 @@ void predict_rows(PredictArgs a, const Features& t, hipStream_t s,
         a.sqt = t.sq.p;
         a.m = t.n;
         a.row_base = 0;
-        // (a buffer of more than 2 MB takes 50 us to allocate and free, more
-        // than the two kernels gain on rows of up to 128 features: 300 x 128
-        // against 6600 support rows 133 -> 153 us)
-        const int64_t few = predict_few_floats(a.nsv, t.n, t.ldp);
-        if (few > 0 && (few <= (int64_t)1 << 19 || t.ldp > 128)) {
+        const int64_t few = few_floats(a.nsv, t.n, t.ldp);
+        if (few > 0) {
             DevBuf<float> kbuf((size_t)few);
             launch_predict_few(a, kbuf.p, s);
             HIP_TRY(hipStreamSynchronize(s));

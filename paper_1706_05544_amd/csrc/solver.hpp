@@ -171,6 +171,10 @@ void load_features(const svm_matrix* M, Features& f, Context& cx,
 
 int64_t padded_ld(int64_t d);
 
+// Whether M is dense device input already in the padded layout (ld = ldp = d,
+// 16-byte aligned), which is used where it is.
+bool padded_in_place(const svm_matrix* M);
+
 struct SolveOptions {
     int32_t type;
     int32_t kernel, degree;
@@ -446,6 +450,12 @@ void build_model(svm_model& m, Context& cx, const Features& f,
 // the model's statistics first when the model was trained on scaled data.
 void predict_device(const svm_model& mdl, Context& cx, Features& t,
                     double* out);
+
+// The whole of svm_predict (labels null) or svm_predict_labels (decision
+// null) on rows for which padded_in_place(), by a model that is not scaled;
+// outputs in device memory, written only when every value of X is finite.
+void predict_in_place(const svm_model& mdl, Context& cx, const svm_matrix* X,
+                      double* decision, int32_t* labels);
 
 // Allocation-free decision values (noalloc.hip): the m dense rows of X
 // (device, leading dimension ld) staged in a static per-device array of
