@@ -16,11 +16,12 @@
 // blocks.
 //
 // Measured (MI355X, us an outer iteration, two-launch loop -> this): eps-SVR
-// 4000 x 50 24.0 -> 8.0 (3 blocks), 1501 x 50 24.6 -> 6.8 (1 block); C-SVC
+// 4000 x 50 24.0 -> 8.2 (3 blocks), 1501 x 50 24.6 -> 6.8 (1 block); C-SVC
 // 20000 x 128 25.3 -> 13.3 with the 1 ms of k_gram in it (11 blocks).  Of
-// the 8.0: update and keys 1.2, bound 0.4, candidates 0.6, rank and exchange
-// 1.6, K_BB and alpha (with the working set built beside it) 1.1, curvature
-// table 0.7, 6.8 subproblem steps 1.7, results 0.6.
+// the 8.2: update and keys 1.2, bound 0.4, candidates 0.6, rank and exchange
+// 1.8 (0.2 of it alpha in the exchange), K_BB and alpha (with the working set
+// built beside it) 1.1, curvature table 0.7, 6.8 subproblem steps 1.7,
+// results 0.6.
 //
 // The working sets, the kernel values (the same matrix-core order), the
 // subproblem and the fp64 order of the update are those of the two-launch
@@ -149,9 +150,15 @@ namespace {
 
 constexpr int kWaves = kSelThreads / 64;
 constexpr int kRowWavesRes = kWaves - 1;  // waves that hold rows
-// words an exchanged candidate takes: the two halves of its key and its
-// variable, each in a 64-bit word with the iteration it belongs to
-constexpr int kXchWords = 3;
+// Fields of an exchanged candidate: the two halves of its key, its variable,
+// the two halves of its alpha, each the low half of a 64-bit word whose high
+// half is the iteration it belongs to.  A block's words: field by field, 16
+// lanes each (up winners, then low winners).
+constexpr int kXchFields = 5;
+constexpr int kXchBlock = kXchFields * 16;
+// words a thread takes of the exchange of kResBlocks blocks
+constexpr int kXchMost =
+    (kResBlocks * kXchBlock + kSelThreads - 1) / kSelThreads;
 // candidates per side ranked by pairs (more: rounds over the block)
 constexpr int kResCand = 256;
 
@@ -208,7 +215,16 @@ __device__ bool resident_start(uint32_t* hs, int R, uint64_t wait)
 }  // namespace
 
 // Dynamic LDS: the state byte of each of the block's variables (copy (i,-)
-// of eps-SVR kResRows bytes later), then the responses of its rows.
+// of eps-SVR kResRows bytes later), then the responses of its rows, then the
+// alpha of its variables (copies as the state bytes).
+//
+// Alpha in memory is read before the first iteration and written after the
+// last, by the block that holds the variable.  In between a candidate's alpha
+// travels with it through the exchange: the words of iteration t hold the
+// value before t, and they are not written again before t + 2, so a block
+// that is late finds it as it was, however far the owner of the variable has
+// got with its own iteration t.  (Read from memory, nothing would order it
+// before the owner's store at the end of t.)
 //
 // Waves 1 .. 15 hold the rows, two consecutive ones a thread, dealt evenly to
 // the waves (four rows a thread took 3.1 us for the update and the keys of
@@ -227,6 +243,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
     __shared__ int32_t upi[8], loi[8];
     __shared__ double svk[2][kResCand];
     __shared__ int32_t svi[2][kResCand];
+    __shared__ double sva[2][kResCand];  // R > 1: alpha of exchanged ones
+    __shared__ int32_t src[2][8];        // R > 1: the winners' places there
     __shared__ int32_t nsv[2];
     __shared__ double rk[2][kWaves];
     __shared__ int32_t ri[2][kWaves];
@@ -264,7 +282,6 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
     const int n = (int)a.n;
     const int64_t ldc = a.ldc;
     const Glob<const float> K = as_global(P.K);
-    const Glob<uint64_t> alpha = as_global((uint64_t*)P.alpha);
     const double eps = P.eps;
     const int max_inner = P.max_inner;
     const int64_t iter0 = ws->iter;
@@ -295,11 +312,16 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
             if (j < nr) z[j] = P.z[row + j];
     }
     double* Fl = reinterpret_cast<double*>(stl + NC * kResRows);
+    double* All = Fl + kResRows;
     for (int e = tid; e < kResRows; e += kSelThreads) {
         const bool in = e < 2 * nu && r0 + e < n;
         Fl[e] = in ? P.F[r0 + e] : 0.0;
         stl[e] = in ? P.st[r0 + e] : (uint8_t)0;
-        if (SVR) stl[kResRows + e] = in ? P.st[n + r0 + e] : (uint8_t)0;
+        All[e] = in ? P.alpha[r0 + e] : 0.0;
+        if (SVR) {
+            stl[kResRows + e] = in ? P.st[n + r0 + e] : (uint8_t)0;
+            All[kResRows + e] = in ? P.alpha[n + r0 + e] : 0.0;
+        }
     }
     if (tid < 128) (&rmax[0][0])[tid] = -INFINITY;  // (wave 0 holds no rows)
     __syncthreads();
@@ -309,6 +331,10 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
     auto cand = [&](int c, double& key, int32_t& idx) {
         key = c < half ? upk[c] : (c < 2 * half ? lok[c - half] : -INFINITY);
         idx = c < half ? upi[c] : (c < 2 * half ? loi[c - half] : INT_MAX);
+    };
+    // place of variable t of this block in stl and All
+    auto local = [&](int32_t t) {
+        return SVR && t >= n ? t - n - r0 + kResRows : t - r0;
     };
     // The steps every wave takes part in: the candidates at or above the
     // bound ranked, and with R > 1 the blocks' lists exchanged through
@@ -360,41 +386,71 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
         if (R > 1) {
             const uint32_t tag = (uint32_t)(iter0 + it + 1);
             const Glob<uint64_t> xb =
-                as_global(P.xch) +
-                (size_t)(tag & 1u) * R * 2 * half * kXchWords;
+                as_global(P.xch) + (size_t)(tag & 1u) * R * kXchBlock;
             if (wave == 0 && lane < 2 * half) {
                 const bool lo = lane >= half;
                 const int k = lo ? lane - half : lane;
-                const uint64_t kb =
-                    __builtin_bit_cast(uint64_t, lo ? lok[k] : upk[k]);
-                const uint32_t ix = (uint32_t)(lo ? loi[k] : upi[k]);
+                const double key = lo ? lok[k] : upk[k];
+                const int32_t idx = lo ? loi[k] : upi[k];
+                const double al =
+                    key == -INFINITY ? 0.0 : All[local(idx)];
+                const uint64_t kb = __builtin_bit_cast(uint64_t, key);
+                const uint64_t ab = __builtin_bit_cast(uint64_t, al);
                 const uint64_t tg = (uint64_t)tag << 32;
-                const Glob<uint64_t> w =
-                    xb + ((size_t)blk * 2 * half + lane) * kXchWords;
+                const Glob<uint64_t> w = xb + (size_t)blk * kXchBlock + lane;
                 agent_store(w, tg | (uint32_t)kb);
-                agent_store(w + 1, tg | (uint32_t)(kb >> 32));
-                agent_store(w + 2, tg | ix);
+                agent_store(w + 16, tg | (uint32_t)(kb >> 32));
+                agent_store(w + 32, tg | (uint32_t)idx);
+                agent_store(w + 48, tg | (uint32_t)ab);
+                agent_store(w + 64, tg | (uint32_t)(ab >> 32));
             }
-            for (int e = tid; e < R * 2 * half; e += kSelThreads) {
-                const Glob<const uint64_t> w = xb + (size_t)e * kXchWords;
-                uint64_t w0, w1, w2;
+            // J words a thread, requested together
+            auto take = [&](auto words) {
+                constexpr int J = decltype(words)::value;
+                uint64_t v[J] = {};
+                bool use[J];
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int e = tid + j * kSelThreads;
+                    use[j] = e < R * kXchBlock && (e & 15) < 2 * half;
+                }
+                bool wait;
                 do {
-                    w0 = agent_load(w);
-                    w1 = agent_load(w + 1);
-                    w2 = agent_load(w + 2);
-                } while ((uint32_t)(w0 >> 32) != tag ||
-                         (uint32_t)(w1 >> 32) != tag ||
-                         (uint32_t)(w2 >> 32) != tag);
-                const int b = e / (2 * half), l = e - b * 2 * half;
-                const int side = l >= half ? 1 : 0;
-                const int pos = b * half + (side ? l - half : l);
-                svk[side][pos] = __builtin_bit_cast(
-                    double, (w1 << 32) | (uint64_t)(uint32_t)w0);
-                svi[side][pos] = (int32_t)(uint32_t)w2;
+                    wait = false;
+#pragma unroll
+                    for (int j = 0; j < J; ++j)
+                        if (use[j]) v[j] = agent_load(xb + tid + j * kSelThreads);
+#pragma unroll
+                    for (int j = 0; j < J; ++j)
+                        wait |= use[j] && (uint32_t)(v[j] >> 32) != tag;
+                } while (wait);
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+                    if (use[j]) {
+                        const int e = tid + j * kSelThreads, l = e & 15;
+                        const int b = (e >> 4) / kXchFields;
+                        const int f = (e >> 4) - kXchFields * b;
+                        const int side = l >= half ? 1 : 0;
+                        const int pos = b * half + (side ? l - half : l);
+                        const uint32_t x = (uint32_t)v[j];
+                        char* to =
+                            f < 2 ? (char*)&svk[side][pos] + 4 * f
+                            : f == 2 ? (char*)&svi[side][pos]
+                                     : (char*)&sva[side][pos] + 4 * (f - 3);
+                        __builtin_memcpy(to, &x, 4);
+                    }
+            };
+            if (R * kXchBlock <= kSelThreads)
+                take(std::integral_constant<int, 1>{});
+            else
+                take(std::integral_constant<int, kXchMost>{});
+            if (a.lag && blk == R - 1) {  // (developer override)
+                const uint64_t t0 = wall_clock64();
+                while (wall_clock64() - t0 < a.lag) __builtin_amdgcn_s_sleep(1);
             }
             __syncthreads();
             rank_lists(svk, svi, R * half, R * half, half, upk, upi, lok, loi,
-                       tid);
+                       tid, src[0], src[1]);
             __syncthreads();
         }
         return M0 <= kResCand && M1 <= kResCand;
@@ -499,20 +555,22 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
                         kb == -INFINITY ? 0 : (SVR && ib >= n ? ib - n : ib);
                     kbb[ca][cb] = K[(int64_t)sa * ldc + sb];
                 } else if (wave == 12 && lane < 16) {
-                    // their alpha (written by whichever block holds the
-                    // variable, so read past the caches), labels and first
-                    // use
+                    // their alpha, labels and first use
                     double key;
                     int32_t idx;
                     cand(lane, key, idx);
                     const bool ok = key != -INFINITY;
                     const int32_t t = ok ? idx : 0;
                     const int32_t smp = SVR && t >= n ? t - n : t;
-                    const uint64_t ab = agent_load(alpha + t);
+                    const int low = lane >= half ? 1 : 0;
+                    const double al =
+                        !ok     ? 0.0
+                        : R > 1 ? sva[low][src[low][low ? lane - half : lane]]
+                                : All[local(t)];
                     const float zb = as_global(P.z)[smp];
                     int32_t seen = 0;
                     if (blk == 0) seen = as_global(P.seen)[smp];
-                    shAl[lane] = __builtin_bit_cast(double, ab);
+                    shAl[lane] = al;
                     const bool yp = SVR ? t < n : zb > 0.0f;
                     shY[lane] = yp ? 1.0f : -1.0f;
                     shSeen[lane] = seen;
@@ -575,8 +633,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
             // (2) a bound from below on the half-th best key of each side:
             // the half-th largest of the waves' maxima (distinct variables).
             // Row 0 takes the up side, row 1 the low side, a lane a wave.
-            // alpha stored in the last iteration is out before it is read
-            // again (and before the words that let other blocks read it)
+            // (the first uses stored in the last iteration are out before
+            // they are read again)
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt(kVmcnt0);
             asm volatile("" ::: "memory");
@@ -787,9 +845,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
             __builtin_amdgcn_wave_barrier();
             if (own) {
                 if (o >= 0 && o < 2 * nu) {
-                    agent_store(alpha + t, __builtin_bit_cast(uint64_t, al));
-                    stl[(SVR && t >= n ? kResRows : 0) + o] =
-                        state_bits(yv, al, C);
+                    All[local(t)] = al;
+                    stl[local(t)] = state_bits(yv, al, C);
                 }
                 if (SVR) shDc[p] = dc;
             }
@@ -851,13 +908,17 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
         if (r0 + e < n) {
             P.F[r0 + e] = Fl[e];
             P.st[r0 + e] = stl[e];
-            if (SVR) P.st[n + r0 + e] = stl[kResRows + e];
+            P.alpha[r0 + e] = All[e];
+            if (SVR) {
+                P.st[n + r0 + e] = stl[kResRows + e];
+                P.alpha[n + r0 + e] = All[kResRows + e];
+            }
         }
 }
 
-size_t resident_xch_words(int R, int half)
+size_t resident_xch_words(int R)
 {
-    return (size_t)2 * R * 2 * half * kXchWords;
+    return (size_t)2 * R * kXchBlock;
 }
 
 void launch_resident(const ResidentArgs& a, int problems, bool svr,
@@ -865,10 +926,10 @@ void launch_resident(const ResidentArgs& a, int problems, bool svr,
 {
     if (problems <= 0) return;
     const int64_t units = (a.n + 1) / 2;
-    if (a.R < 1 || a.half < 1 || a.half > 8 || a.R * a.half > kResCand ||
+    if (a.R < 1 || a.R > kResBlocks || a.half < 1 || a.half > 8 || a.R * a.half > kResCand ||
         (units + a.R - 1) / a.R > kResUnits)
         throw Error{SVM_E_INTERNAL, "bad resident launch"};
-    const size_t lds = (size_t)(svr ? 10 : 9) * kResRows;
+    const size_t lds = (size_t)(svr ? 26 : 17) * kResRows;
     const void* fn = svr ? (const void*)k_resident<true>
                          : (const void*)k_resident<false>;
     if (!raise_dynamic_lds(fn, lds))

@@ -20,7 +20,7 @@ struct ResidentProblem {
     const float* z;       // labels (C-SVC) or targets (eps-SVR)
     WorkingSet* ws;
     int32_t* seen;        // n: -1 until the sample has been used
-    uint64_t* xch;        // R > 1: resident_xch_words, zero before a solve
+    uint64_t* xch;        // R > 1: resident_xch_words(R), zero before a solve
     double C, eps, tol, inner_ratio;
     int64_t max_iter;
     int32_t max_inner;
@@ -32,12 +32,15 @@ struct ResidentArgs {
     int32_t R, half;
     int32_t iters;        // outer iterations of this launch, at most
     uint64_t wait;        // R > 1: for the blocks to start, 100 MHz ticks
+    uint64_t lag;         // R > 1: how long each problem's last block waits
+                          // between taking the other blocks' candidates and
+                          // using them (tests; 0: not at all)
 };
 
 // every K(x_i, x_j): K[i * ldc + j], the values of the row kernel bit for bit
 void launch_gram(const float* X, const float* sq, int64_t n, int64_t ldp,
                  const KernelFn& kf, float* K, int64_t ldc, hipStream_t s);
-size_t resident_xch_words(int R, int half);
+size_t resident_xch_words(int R);
 void launch_resident(const ResidentArgs& a, int problems, bool svr,
                      hipStream_t s);
 

@@ -138,14 +138,17 @@ __device__ __forceinline__ void pair_rank_top(const double (*k)[kSurv],
 }
 
 // the rank of every entry of both sides' lists among its side's, and the
-// first `half` of each list into (ku, iu) and (kl, il): waves 0 .. 7 take
-// side 0, the others side 1, 16 lanes an entry
+// first `half` of each list into (ku, iu) and (kl, il), their places in the
+// lists into pu and pl where given: waves 0 .. 7 take side 0, the others
+// side 1, 16 lanes an entry
 template <int CAP>
 __device__ __forceinline__ void rank_lists(const double (*k)[CAP],
                                            const int32_t (*i)[CAP],
                                            int M0, int M1, int half,
                                            double* ku, int32_t* iu, double* kl,
-                                           int32_t* il, int tid)
+                                           int32_t* il, int tid,
+                                           int32_t* pu = nullptr,
+                                           int32_t* pl = nullptr)
 {
     const int side = tid >> 9, l = tid & 15;
     const int M = side ? M1 : M0;
@@ -160,6 +163,7 @@ __device__ __forceinline__ void rank_lists(const double (*k)[CAP],
         if (l == 0 && c < half) {
             (side ? kl : ku)[c] = ke;
             (side ? il : iu)[c] = ie;
+            if (pu) (side ? pl : pu)[c] = e;
         }
     }
 }

@@ -1017,7 +1017,7 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
         rc.full = true;
     }
     const int R = (int)resident_blocks(n);
-    const size_t xw = resident_xch_words(R, s0.half_);
+    const size_t xw = resident_xch_words(R);
     DevBuf<uint64_t> xch(R > 1 ? xw * G : 1);
     DevBuf<uint32_t> hs((size_t)4 * G);  // two launches in flight
     DevBuf<ResidentProblem> pd((size_t)G);
@@ -1060,6 +1060,9 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
     a.wait = 2000000;  // 20 ms
     if (const char* e = getenv("SVM_RESIDENT_WAIT"))  // developer override
         a.wait = (uint64_t)std::max(0, atoi(e));
+    // developer override: 10 ns each, at most 1 ms
+    if (const char* e = getenv("SVM_RESIDENT_LAG"))
+        a.lag = (uint64_t)std::min(100000, std::max(0, atoi(e)));
     const bool svr = s0.o_.type == SVM_EPS_SVR;
 
     HostBuf<WorkingSet> hw((size_t)2 * G);

@@ -9,6 +9,9 @@ blocks that exchange their candidates, the smallest problems, working sets
 of 2 to 16, ties of every key (alpha = 0) past the candidate list, eps-SVR
 with both copies of a sample in a working set.
 """
+import os
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
@@ -54,6 +57,44 @@ def test_same_bits_as_the_two_launch_loop(name, n, kw):
     _same(workloads.make(name, n=n, n_test=4), **kw)
 
 
+def _rows(n, d, svr=False):
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d), dtype=np.float32)
+    if svr:
+        y = np.sin(3 * X[:, 0]) + 0.1 * rng.standard_normal(n)
+    else:
+        y = np.where(rng.random(n) < 0.5, 1.0, -1.0)
+        X += np.float32(2.25 / np.sqrt(d)) * y[:, None].astype(np.float32)
+    return SimpleNamespace(X=X, y=y.astype(np.float32), type=int(svr),
+                           C=10.0 if svr else 1.0, eps=0.1, gamma=0.0,
+                           tol=1e-3)
+
+
+@pytest.mark.parametrize("n,d,svr,kw", [
+    (2000, 20, False, {}),             # two blocks
+    (4100, 20, True, {}),              # three
+    (15361, 7, False, dict(max_iter=400)),               # nine
+    (23041, 5, True, dict(max_iter=300)),                # thirteen
+    (61440, 4, False, dict(max_iter=300)),               # 32, the most
+    (61439, 4, True, dict(max_iter=300, working_set=12)),
+])
+def test_late_block(n, d, svr, kw, monkeypatch):
+    # Every block solves the subproblem of an iteration for itself.  One that
+    # takes up the exchanged candidates 20 us late, when the others are past
+    # their iteration's end, has to find alpha as it was before it.
+    w = _rows(n, d, svr)
+    i0, a0 = _train(w, cache_bytes=-1, **kw)
+    for lag in ("2000", None):
+        if lag:
+            monkeypatch.setenv("SVM_RESIDENT_LAG", lag)
+        else:
+            monkeypatch.delenv("SVM_RESIDENT_LAG")
+        i1, a1 = _train(w, **kw)
+        np.testing.assert_array_equal(a1, a0)
+        for k in SAME:
+            assert i1[k] == i0[k], k
+
+
 def test_duplicate_rows():
     # equal rows: zero curvature, equal keys all along
     w = workloads.make("C2", n=2200, n_test=4)
@@ -64,7 +105,6 @@ def test_duplicate_rows():
 def test_launch_called_off():
     # no time to wait for a problem's blocks: launches are called off and the
     # two-launch loop takes over from the state they left
-    import os
     w = workloads.make("C2", n=4100, n_test=4)
     i0, a0 = _train(w, cache_bytes=-1)
     os.environ["SVM_RESIDENT_WAIT"] = "0"
