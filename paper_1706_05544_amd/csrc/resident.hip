@@ -62,6 +62,9 @@ __global__ __launch_bounds__(256, 2) void k_gram(const float* X,
     while (bj * (bj + 1) / 2 > b) --bj;
     while ((bj + 1) * (bj + 2) / 2 <= b) ++bj;
     const int64_t bi = b - bj * (bj + 1) / 2;
+    // row n: zeros (k_resident reads it for slots that are not used)
+    if (bi == bj && tid < kGramTile && bj * kGramTile + tid < ldc)
+        K[n * ldc + bj * kGramTile + tid] = 0.0f;
     const int64_t i0 = bi * kGramTile + 64 * (wave >> 1);
     const int64_t j0 = bj * kGramTile + 64 * (wave & 1);
     if (i0 >= n || j0 >= n) return;
@@ -578,7 +581,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
             __syncthreads();
             if (__builtin_amdgcn_readfirstlane(shGo) == 0) break;
             // (7) the kernel values of this thread's rows, in flight while
-            // wave 0 solves (slots past nS: any row, their change is 0)
+            // wave 0 solves (slots past nS: the row of zeros, as the change
+            // is 0 and a sample's row may hold an infinity)
             // (already as fp64: converting them is then not on the chain)
             typedef float floatx2 __attribute__((ext_vector_type(2)));
             double kd[16][2];
@@ -737,9 +741,10 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
                         shSlot[c] = slot;
                         shS[slot] = smp;
                     }
-                    // ranks past nB and slots past theirs: any (not used)
+                    // ranks past nB: any (not used); slots past theirs: the
+                    // row of zeros
                     if (lane >= nB) shCand[lane] = 0;
-                    if (lane >= __popc(firstm)) shS[lane] = 0;
+                    if (lane >= __popc(firstm)) shS[lane] = n;
                 }
             }
             if (lane == 0) {

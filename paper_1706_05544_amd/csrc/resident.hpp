@@ -13,7 +13,7 @@ constexpr int kResUnits = kSelThreads - 64;
 constexpr int kResRows = 2 * kResUnits;
 constexpr int kResBlocks = 32;  // of one problem, at most
 struct ResidentProblem {
-    const float* K;       // n rows of ldc floats: K(x_s, .)
+    const float* K;       // n rows of ldc floats: K(x_s, .), and one of zeros
     double* F;
     double* alpha;
     uint8_t* st;
@@ -37,7 +37,8 @@ struct ResidentArgs {
                           // using them (tests; 0: not at all)
 };
 
-// every K(x_i, x_j): K[i * ldc + j], the values of the row kernel bit for bit
+// every K(x_i, x_j): K[i * ldc + j], the values of the row kernel bit for bit,
+// and row n: zeros
 void launch_gram(const float* X, const float* sq, int64_t n, int64_t ldp,
                  const KernelFn& kf, float* K, int64_t ldc, hipStream_t s);
 size_t resident_xch_words(int R);

@@ -843,12 +843,20 @@ void k_rows(RowArgs a)
                                         a.cache + (int64_t)csb * a.ldc + rw0 +
                                         lr) = make_float4(kv[b][0], kv[b][1],
                                                           kv[b][2], kv[b][3]);
-                                if (INS && hs_in[b] >= 0) {
-                                    // a slot whose row is cached takes that
-                                    kv[b][0] = hv[b].x;
-                                    kv[b][1] = hv[b].y;
-                                    kv[b][2] = hv[b].z;
-                                    kv[b][3] = hv[b].w;
+                                if (INS) {
+                                    // a slot whose row is cached takes that,
+                                    // one that the working set does not use
+                                    // (its column is computed ahead, and may
+                                    // have overflowed) nothing
+                                    const bool hit = hs_in[b] >= 0;
+                                    const bool own = b * 16 + nl < nS;
+                                    const float h[4] = {hv[b].x, hv[b].y,
+                                                        hv[b].z, hv[b].w};
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v)
+                                        kv[b][v] = hit   ? h[v]
+                                                   : own ? kv[b][v]
+                                                         : 0.0f;
                                 }
                             }
                             if (INS) hfetch(pti + 1);

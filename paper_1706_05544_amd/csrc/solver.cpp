@@ -325,8 +325,10 @@ void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx)
     if (slots <= kMaxQ && slots < n) return;
     if (slots < 2) return;
     // (+16 floats: the row kernel reads whole 16-row tiles, up to 15 rows
-    // past the last sample, and the last row has nothing after it)
-    c.rows.alloc((size_t)(slots * c.ldc + 16), cx.device);
+    // past the last sample, and the last row has nothing after it; with all
+    // rows in the cache one more, the row of zeros of k_resident)
+    c.rows.alloc((size_t)((slots + (slots >= n ? 1 : 0)) * c.ldc + 16),
+                 cx.device);
     c.slot_of.alloc((size_t)n);
     c.owner.alloc((size_t)slots);
     c.clock.alloc(1);
