@@ -49,7 +49,7 @@ struct WorkingSet {
     int32_t done;      // 0 running, 1 converged (gap <= tol), 2 iteration cap
     int32_t nB;        // variables in B
     int32_t nS;        // distinct samples of B (slots)
-    int32_t pad0;
+    int32_t called_off; // k_resident launches that did not start
     int64_t iter;      // outer iterations performed
     int64_t rows;      // kernel rows evaluated (sum of nS)
     double gap, m, M;
@@ -60,7 +60,8 @@ struct WorkingSet {
     double coef[kMaxQ];   // change of the expansion coefficient per slot
     double alphaB[kMaxQ]; // new alpha_B (written by the solve)
     int32_t steps;        // inner steps of the last subproblem
-    int32_t pad1;
+    int32_t res_launches; // k_resident launches that started
+    int64_t res_iters;    // outer iterations they did
     int64_t inner_total;  // inner steps summed over iterations
     int64_t rescans;      // iterations that rescanned exhausted blocks
     int64_t slow_selects; // iterations that fell back to a full scan

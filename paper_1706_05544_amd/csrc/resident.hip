@@ -190,8 +190,10 @@ __device__ __forceinline__ void agent_store(Glob<uint64_t> p, uint64_t v)
 // when the last one has said so.  If they do not all arrive in time (other
 // work holds the compute units), the launch is called off: one atomic
 // decides between the two, so every block of the problem does the same.
+// (No time at all: it is called off without being tried.)
 __device__ bool resident_start(uint32_t* hs, int R, uint64_t wait)
 {
+    if (wait == 0) return false;
     const uint32_t old = __hip_atomic_fetch_add(
         &hs[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (old + 1 == (uint32_t)R) {
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
         if (tid == 0) shGo = resident_start(a.hs + 2 * prob, R, a.wait) ? 1 : 0;
         __syncthreads();
         if (!__builtin_amdgcn_readfirstlane(shGo)) {
-            if (blk == 0 && tid == 0) ws->pad0 = 1;  // called off
+            if (blk == 0 && tid == 0) ws->called_off += 1;
             return;
         }
     }
@@ -894,6 +896,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
         }
         if (blk == 0 && tid == 0) {
             ws->iter = iter0 + d_iter;
+            ws->res_iters += d_iter;
+            ws->res_launches += 1;
             ws->rows += d_rows;
             ws->inner_total += d_inner;
             ws->cache_served += d_served;

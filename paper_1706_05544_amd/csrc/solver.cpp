@@ -1090,6 +1090,8 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
                                    st));
         HIP_TRY(hipEventRecord(ev.e[slot], st));
     };
+    std::vector<int32_t> off0((size_t)G);  // called off before
+    for (int p = 0; p < G; ++p) off0[(size_t)p] = g[p]->off_seen_;
     bool ok = true;
     try {
         enqueue(0);
@@ -1101,7 +1103,7 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
             for (int p = 0; p < G; ++p) {
                 const WorkingSet& w = hw.p[(size_t)cur * G + p];
                 run |= !w.done;
-                if (w.pad0) ok = false;
+                if (w.called_off > off0[(size_t)p]) ok = false;
             }
             if (!run || !ok) break;
             enqueue(cur);
@@ -1117,7 +1119,7 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
         g[p]->read_ws(w);
         g[p]->fill_result(w, r[(size_t)p]);
         conv[(size_t)p] = w.done == 1;
-        if (!ok) launch_fill_i32(&g[p]->ws_.p->pad0, 0, 1, st);
+        g[p]->off_seen_ = w.called_off;
     }
     return ok;
 }
@@ -1302,6 +1304,12 @@ void Solver::finish(SolveResult& r, bool conv, hipEvent_t t0, int max_passes)
     r.cache_filled = w.cache_filled;
     r.iters = w.iter;
     if (const char* e = getenv("SVM_LOG")) {
+        if (atoi(e) > 0 && (w.res_launches > 0 || w.called_off > 0))
+            fprintf(stderr,
+                    "[mi355svm] resident loop: %lld of %lld iterations in %d "
+                    "launches of %d blocks, %d called off\n",
+                    (long long)w.res_iters, (long long)w.iter, w.res_launches,
+                    (int)resident_blocks(n_), w.called_off);
         if (atoi(e) > 0 && fused_ && w.prof[4] > 0) {
             const double k = 10.0 / (double)w.prof[4];  // 100 MHz ticks -> ns
             fprintf(stderr,

@@ -331,6 +331,7 @@ private:
     bool fused_ = false;
     bool resident_ = false;  // the loop is k_resident
     DevBuf<int32_t> seen_;   // its samples used so far
+    int32_t off_seen_ = 0;   // its launches called off so far
     int nbi_ = 0, tilesi_ = 0, tilesk_ = 0;
     DevBuf<double> F2_, irk_;
     DevBuf<int32_t> iri_;

@@ -10,6 +10,7 @@ of 2 to 16, ties of every key (alpha = 0) past the candidate list, eps-SVR
 with both copies of a sample in a working set.
 """
 import os
+import re
 from types import SimpleNamespace
 
 import numpy as np
@@ -30,14 +31,30 @@ def _train(w, **kw):
     return m.info(), nv.svm_model_get(m, 0, with_alpha=True)[2]
 
 
-def _same(w, **kw):
+@pytest.fixture
+def loops(capfd, monkeypatch):
+    """What the trainings since the last call ran as, one after another:
+    (iterations in the resident loop, all iterations, blocks, launches called
+    off) of each that had a resident launch."""
+    monkeypatch.setenv("SVM_LOG", "1")
+
+    def read():
+        err = capfd.readouterr().err
+        found = re.findall(r"resident loop: (\d+) of (\d+) iterations in \d+ "
+                           r"launches of (\d+) blocks, (\d+) called off", err)
+        return [tuple(map(int, f)) for f in found]
+    return read
+
+
+def _same(w, loops, blocks, **kw):
     i0, a0 = _train(w, cache_bytes=-1, **kw)
+    assert loops() == []
     i1, a1 = _train(w, **kw)
     np.testing.assert_array_equal(a1, a0)
     for k in SAME:
         assert i1[k] == i0[k], k
-    # served from the cache: the loop under test ran
-    assert i1["cache_hits"] + i1["cache_fills"] > 0
+    # the loop under test ran, from the first iteration to the last
+    assert loops() == [(i1["iters"], i1["iters"], blocks, 0)]
     return i1
 
 
@@ -53,8 +70,8 @@ def _same(w, **kw):
     ("C1", 1500, dict(max_iter=7)), ("C1", 2000, dict(check_every=3)),
     ("C1", 900, dict(max_inner=1)), ("C1", 1500, dict(scale=1)),
 ])
-def test_same_bits_as_the_two_launch_loop(name, n, kw):
-    _same(workloads.make(name, n=n, n_test=4), **kw)
+def test_same_bits_as_the_two_launch_loop(name, n, kw, loops):
+    _same(workloads.make(name, n=n, n_test=4), loops, -(-n // 1920), **kw)
 
 
 def _rows(n, d, svr=False):
@@ -78,7 +95,7 @@ def _rows(n, d, svr=False):
     (61440, 4, False, dict(max_iter=300)),               # 32, the most
     (61439, 4, True, dict(max_iter=300, working_set=12)),
 ])
-def test_late_block(n, d, svr, kw, monkeypatch):
+def test_late_block(n, d, svr, kw, monkeypatch, loops):
     # Every block solves the subproblem of an iteration for itself.  One that
     # takes up the exchanged candidates 20 us late, when the others are past
     # their iteration's end, has to find alpha as it was before it.
@@ -93,16 +110,27 @@ def test_late_block(n, d, svr, kw, monkeypatch):
         np.testing.assert_array_equal(a1, a0)
         for k in SAME:
             assert i1[k] == i0[k], k
+        assert loops() == [(i1["iters"], i1["iters"], -(-n // 1920), 0)]
 
 
-def test_duplicate_rows():
+def test_more_rows_than_blocks_hold(loops):
+    # one row past 32 blocks: the two-launch loop
+    w = _rows(61441, 4)
+    i0, a0 = _train(w, cache_bytes=-1, max_iter=200)
+    i1, a1 = _train(w, max_iter=200)
+    np.testing.assert_array_equal(a1, a0)
+    assert loops() == []
+    assert i1["cache_fills"] > 0
+
+
+def test_duplicate_rows(loops):
     # equal rows: zero curvature, equal keys all along
     w = workloads.make("C2", n=2200, n_test=4)
     w.X[1100:] = w.X[:1100]
-    _same(w, max_iter=400)
+    _same(w, loops, 2, max_iter=400)
 
 
-def test_launch_called_off():
+def test_launch_called_off(loops):
     # no time to wait for a problem's blocks: launches are called off and the
     # two-launch loop takes over from the state they left
     w = workloads.make("C2", n=4100, n_test=4)
@@ -113,13 +141,15 @@ def test_launch_called_off():
             i1, a1 = _train(w)
             np.testing.assert_array_equal(a1, a0)
             assert i1["iters"] == i0["iters"] and i1["b"] == i0["b"]
+            (done, iters, blocks, off), = loops()
+            assert off > 0 and done == 0 and blocks == 3
     finally:
         del os.environ["SVM_RESIDENT_WAIT"]
 
 
 @pytest.mark.parametrize("name,n,k,lockstep", [
     ("C1", 501, 3, 0), ("C2", 700, 4, 4), ("C1", 4000, 5, 2)])
-def test_cross_validation_side_by_side(name, n, k, lockstep):
+def test_cross_validation_side_by_side(name, n, k, lockstep, loops):
     w = workloads.make(name, n=n, n_test=4)
     kw = dict(k=k, type=w.type, C=w.C, epsilon=w.eps, gamma=w.gamma,
               tol=w.tol, lockstep=lockstep)
@@ -128,9 +158,11 @@ def test_cross_validation_side_by_side(name, n, k, lockstep):
     np.testing.assert_array_equal(D1, D0)
     for key in ("iters", "kernel_rows", "accuracy", "mse", "status"):
         assert s1[key] == s0[key], key
+    ran = loops()
+    assert len(ran) == k and sum(r[0] for r in ran) == s1["iters"]
 
 
-def test_ovr_and_tuning_side_by_side():
+def test_ovr_and_tuning_side_by_side(loops):
     w = workloads.make("C4", n=2003, n_test=50)
     kw = dict(C=w.C, gamma=w.gamma, tol=w.tol)
     m0 = nv.svm_train_ovr(w.X, w.y, w.n_classes, cache_bytes=-1, **kw)
@@ -139,6 +171,8 @@ def test_ovr_and_tuning_side_by_side():
         np.testing.assert_array_equal(
             nv.svm_model_get(m1, c, with_alpha=True)[2],
             nv.svm_model_get(m0, c, with_alpha=True)[2])
+    assert [r[0] for r in loops()] == [m1.info(c)["iters"]
+                                       for c in range(w.n_classes)]
     w = workloads.c1(n=900, n_test=4)
     kw = dict(k=3, C=np.array([0.1, 1.0, 10.0]),
               gamma=np.array([0.05, 0.05, 0.2]), tol=w.tol)
@@ -146,3 +180,4 @@ def test_ovr_and_tuning_side_by_side():
     e1, b1 = nv.svm_tune(w.X, w.y, **kw)
     np.testing.assert_array_equal(e1, e0)
     assert b0 == b1
+    assert len(loops()) == 9  # three folds of each
