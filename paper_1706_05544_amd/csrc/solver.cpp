@@ -953,6 +953,9 @@ bool Solver::run_loop_fused(SolveResult& r)
 // as fast), and the blocks of one problem fit the chip.
 constexpr double kGramWork = 6e10;
 
+// Launches called off in one loop after which it is left (see run_resident).
+constexpr int kResOff = 3;
+
 // Blocks of a problem: as few as hold its rows (the exchange between blocks
 // costs about 1.5 us an iteration, whatever their number up to 4).
 static int64_t resident_blocks(int64_t n)
@@ -1066,6 +1069,8 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
     if (const char* e = getenv("SVM_RESIDENT_LAG"))
         a.lag = (uint64_t)std::min(100000, std::max(0, atoi(e)));
     const bool svr = s0.o_.type == SVM_EPS_SVR;
+    int off_first = 0;  // developer override: launches to call off
+    if (const char* e = getenv("SVM_RESIDENT_OFF")) off_first = atoi(e);
 
     HostBuf<WorkingSet> hw((size_t)2 * G);
     struct Events {
@@ -1083,40 +1088,59 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
         if (R > 1)
             HIP_TRY(hipMemsetAsync(a.hs, 0, (size_t)2 * G * sizeof(uint32_t),
                                    st));
-        launch_resident(a, G, svr, st);
+        ResidentArgs b = a;
+        if (off_first-- > 0) b.wait = 0;
+        launch_resident(b, G, svr, st);
         for (int p = 0; p < G; ++p)
             HIP_TRY(hipMemcpyAsync(&hw.p[(size_t)slot * G + p], g[p]->ws_.p,
                                    sizeof(WorkingSet), hipMemcpyDeviceToHost,
                                    st));
         HIP_TRY(hipEventRecord(ev.e[slot], st));
     };
+    // A launch that was called off left the states as they were: it is tried
+    // again, one at a time until one has run, and given up for the rest of
+    // the loop when that has happened kResOff times (20 ms each).
     std::vector<int32_t> off0((size_t)G);  // called off before
     for (int p = 0; p < G; ++p) off0[(size_t)p] = g[p]->off_seen_;
-    bool ok = true;
+    std::vector<WorkingSet> wl((size_t)G);
+    bool ok = true, again = false;
+    int offs = 0;
     try {
-        enqueue(0);
-        enqueue(1);
-        int cur = 0;
         for (;;) {
-            HIP_TRY(hipEventSynchronize(ev.e[cur]));
-            bool run = false;
-            for (int p = 0; p < G; ++p) {
-                const WorkingSet& w = hw.p[(size_t)cur * G + p];
-                run |= !w.done;
-                if (w.called_off > off0[(size_t)p]) ok = false;
+            enqueue(0);
+            if (!again) enqueue(1);
+            bool run, off;
+            for (int cur = 0;; cur ^= 1) {
+                HIP_TRY(hipEventSynchronize(ev.e[cur]));
+                run = off = false;
+                for (int p = 0; p < G; ++p) {
+                    const WorkingSet& w = hw.p[(size_t)cur * G + p];
+                    run |= !w.done;
+                    off |= w.called_off > off0[(size_t)p];
+                }
+                if (!run || off || again) break;
+                enqueue(cur);
             }
-            if (!run || !ok) break;
-            enqueue(cur);
-            cur ^= 1;
+            cx.sync();
+            run = false;
+            for (int p = 0; p < G; ++p) {
+                g[p]->read_ws(wl[(size_t)p]);
+                run |= !wl[(size_t)p].done;
+                off0[(size_t)p] = wl[(size_t)p].called_off;
+            }
+            again = off;
+            if (!run) break;
+            if (off && ++offs >= kResOff) {
+                ok = false;
+                break;
+            }
         }
     } catch (...) {
         cx.sync();
         throw;
     }
-    cx.sync();
     for (int p = 0; p < G; ++p) {
-        WorkingSet w;
-        g[p]->read_ws(w);
+        const WorkingSet& w = wl[(size_t)p];
         g[p]->fill_result(w, r[(size_t)p]);
         conv[(size_t)p] = w.done == 1;
         g[p]->off_seen_ = w.called_off;

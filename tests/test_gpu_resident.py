@@ -147,6 +147,17 @@ def test_launch_called_off(loops):
         del os.environ["SVM_RESIDENT_WAIT"]
 
 
+def test_launch_called_off_once(loops, monkeypatch):
+    # the resident loop takes the solve up again
+    w = workloads.make("C2", n=4100, n_test=4)
+    i0, a0 = _train(w, cache_bytes=-1)
+    for first in (1, 2):  # (two launches are queued, then one at a time)
+        monkeypatch.setenv("SVM_RESIDENT_OFF", str(first))
+        i1, a1 = _train(w)
+        np.testing.assert_array_equal(a1, a0)
+        assert loops() == [(i0["iters"], i0["iters"], 3, first)]
+
+
 @pytest.mark.parametrize("name,n,k,lockstep", [
     ("C1", 501, 3, 0), ("C2", 700, 4, 4), ("C1", 4000, 5, 2)])
 def test_cross_validation_side_by_side(name, n, k, lockstep, loops):
