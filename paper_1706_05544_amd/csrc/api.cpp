@@ -438,7 +438,7 @@ svm_status svm_train_ovr(const svm_matrix* X, const int32_t* labels,
             gp.push_back(ss.back().get());
         }
         const std::vector<msvm::SolveResult> rr =
-            res_fit ? msvm::Solver::train_resident(gp)
+            res_fit ? msvm::Solver::train_resident(gp, lock_group(p, f))
                     : msvm::Solver::train_lockstep(gp);
         for (int j = 0; j < G; ++j) collect(c0 + j, *gp[j], rr[(size_t)j]);
     }
@@ -740,7 +740,7 @@ svm_status cv_run_many(CvData& c, const std::vector<svm_params>& ps,
                 gp.push_back(ss.back().get());
             }
             std::vector<msvm::SolveResult> rr;
-            if (res_fit) rr = msvm::Solver::train_resident(gp);
+            if (res_fit) rr = msvm::Solver::train_resident(gp, L);
             else rr.push_back(gp[0]->train());
             for (size_t j = 0; j < gp.size(); ++j)
                 collect(g, (t0 + (int32_t)j) / c.n_out,

@@ -1148,7 +1148,8 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
     return ok;
 }
 
-std::vector<SolveResult> Solver::train_resident(const std::vector<Solver*>& g)
+std::vector<SolveResult> Solver::train_resident(const std::vector<Solver*>& g,
+                                                int lock)
 {
     const size_t G = g.size();
     std::vector<SolveResult> r(G);
@@ -1164,10 +1165,18 @@ std::vector<SolveResult> Solver::train_resident(const std::vector<Solver*>& g)
     std::vector<char> conv(G, 0);
     if (!run_resident(g, r, conv)) {
         s0.leave_resident();
-        for (size_t p = 0; p < G; ++p) {
-            g[p]->resident_ = false;
-            g[p]->launch_keys();
-            conv[p] = g[p]->run_loop(r[p]);
+        for (Solver* s : g) {
+            s->resident_ = false;
+            if (lock > 1) s->cache_ = nullptr;
+        }
+        for (size_t p = 0; p < G; p += (size_t)lock) {
+            const size_t e = std::min(G, p + (size_t)lock);
+            if (e - p > 1) {  // in lockstep, as without the resident loop
+                run_lockstep({g.begin() + p, g.begin() + e}, &r[p], &conv[p]);
+            } else {
+                g[p]->launch_keys();
+                conv[p] = g[p]->run_loop(r[p]);
+            }
         }
     }
     for (size_t p = 0; p < G; ++p) g[p]->finish(r[p], conv[p], t0[p]);
@@ -1388,9 +1397,25 @@ int Solver::lock_capacity(const Features& f, int32_t type)
 std::vector<SolveResult> Solver::train_lockstep(
     const std::vector<Solver*>& g)
 {
-    const int G = (int)g.size();
+    const size_t G = g.size();
     std::vector<SolveResult> res(G);
-    if (G == 0) return res;
+    std::vector<hipEvent_t> t0(G);
+    std::vector<char> conv(G);
+    for (size_t p = 0; p < G; ++p) t0[p] = g[p]->start(false);
+    try {
+        if (G > 0) run_lockstep(g, res.data(), conv.data());
+    } catch (...) {
+        for (auto& e : t0) (void)hipEventDestroy(e);
+        throw;
+    }
+    for (size_t p = 0; p < G; ++p) g[p]->finish(res[p], conv[p], t0[p]);
+    return res;
+}
+
+void Solver::run_lockstep(const std::vector<Solver*>& g, SolveResult* res,
+                          char* conv)
+{
+    const int G = (int)g.size();
     Solver& s0 = *g[0];
     Context& cx = s0.cx_;
     const Features& f = s0.f_;
@@ -1510,9 +1535,8 @@ std::vector<SolveResult> Solver::train_lockstep(
         }
     };
 
-    std::vector<hipEvent_t> t0(G);
-    for (int p = 0; p < G; ++p) t0[p] = g[p]->start(false);
-    // the first candidates: a pass with empty working sets (F + 0)
+    // the first candidates: a pass with empty working sets (F + 0; no
+    // selection has written these states: nS is 0)
     build();
     launch_lock(la, G, (int)nb, svr, st);
 
@@ -1639,26 +1663,19 @@ std::vector<SolveResult> Solver::train_lockstep(
     } catch (...) {
         cx.sync();
         cleanup();
-        for (auto& e : t0) (void)hipEventDestroy(e);
         throw;
     }
     cleanup();
 
-    std::vector<char> conv(G);
     for (int p = 0; p < G; ++p) {
         WorkingSet w;
         g[p]->read_ws(w);
-        SolveResult& r = res[p];
-        r.iters = w.iter;
-        r.gap = w.gap;
-        r.m = w.m;
-        r.M = w.M;
-        r.kernel_rows = w.rows;
-        r.status = w.done == 2 ? SVM_W_MAX_ITER : SVM_OK;
+        g[p]->fill_result(w, res[p]);
         conv[p] = w.done == 1;
     }
-    for (int p = 0; p < G; ++p) g[p]->finish(res[p], conv[p], t0[p]);
-    return res;
+    if (const char* e = getenv("SVM_LOG"))
+        if (atoi(e) > 0)
+            fprintf(stderr, "[mi355svm] lockstep: %d problems\n", G);
 }
 
 void Solver::coefficients(double* c, int32_t stride, int32_t off)

@@ -246,9 +246,12 @@ public:
     static bool resident_may_fit(const SolveOptions& o, const Features& f);
     // Training of several solvers for which resident_fits(), side by side:
     // each has compute units of its own and the same result as alone.  They
-    // share the features, the stream, the type and the kernel matrix.
+    // share the features, the stream, the type and the kernel matrix.  Should
+    // the GPU have no room for it, they go on in lockstep groups of `lock`
+    // (1: one after another; at most lock_capacity(); > 1 needs working sets
+    // of 16).
     static std::vector<SolveResult> train_resident(
-        const std::vector<Solver*>& group);
+        const std::vector<Solver*>& group, int lock);
     // Problems one train_resident call runs side by side.
     static int resident_capacity(int64_t n, int device);
     // Problems one lockstep pass can carry for these features (their
@@ -304,6 +307,9 @@ private:
                              std::vector<SolveResult>& r,
                              std::vector<char>& conv);
     void leave_resident();
+    // the loops of the group's solvers in lockstep, from their states
+    static void run_lockstep(const std::vector<Solver*>& g, SolveResult* res,
+                             char* conv);
     void fill_result(const WorkingSet& w, SolveResult& r) const;
     // one launch per outer iteration: initial records, the loop
     void launch_keys_fused();

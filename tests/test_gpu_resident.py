@@ -158,6 +158,24 @@ def test_launch_called_off_once(loops, monkeypatch):
         assert loops() == [(i0["iters"], i0["iters"], 3, first)]
 
 
+def test_called_off_in_lockstep(capfd, monkeypatch):
+    # who asks for lockstep groups gets them when the resident loop does not
+    # run: 5 trainings in groups of 2, the last one alone
+    w = workloads.make("C1", n=4000, n_test=4)
+    kw = dict(k=5, type=w.type, C=w.C, epsilon=w.eps, gamma=w.gamma,
+              tol=w.tol, lockstep=2)
+    D0, s0 = nv.svm_cross_validate(w.X, w.y, cache_bytes=-1, **kw)
+    monkeypatch.setenv("SVM_RESIDENT_WAIT", "0")
+    monkeypatch.setenv("SVM_LOG", "1")
+    capfd.readouterr()
+    D1, s1 = nv.svm_cross_validate(w.X, w.y, **kw)
+    err = capfd.readouterr().err
+    np.testing.assert_array_equal(D1, D0)
+    assert s1["iters"] == s0["iters"] and s1["status"] == s0["status"]
+    assert err.count("resident loop: 0 of") == 5
+    assert err.count("lockstep: 2 problems") == 2
+
+
 @pytest.mark.parametrize("name,n,k,lockstep", [
     ("C1", 501, 3, 0), ("C2", 700, 4, 4), ("C1", 4000, 5, 2)])
 def test_cross_validation_side_by_side(name, n, k, lockstep, loops):
