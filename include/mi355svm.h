@@ -157,8 +157,10 @@ typedef struct {
                               SVM_E_UNSUPPORTED.  No effect on svm_train.
                               train_ms of a problem then spans its group's
                               run (the groups' problems overlap in time).
-                              Not used where the whole K is in the cache
-                              (cache_bytes) */
+                              Not used where the whole K is computed at
+                              once into the cache (see cache_bytes, whose
+                              memory is then taken and kept; < 0: lockstep
+                              all the same) */
     int32_t fused;         /* 1: every outer iteration as one launch, in
                               which each block merges the selection
                               candidates and solves the subproblem itself

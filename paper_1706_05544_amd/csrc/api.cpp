@@ -722,7 +722,7 @@ svm_status cv_run_many(CvData& c, const std::vector<svm_params>& ps,
             msvm::cache_init(
                 rc, n,
                 msvm::one_launch_loop(o, c.f) ? -1 : ps[(size_t)g].cache_bytes,
-                cx);
+                cx, L > 1);  // (lockstep groups use no cache)
         const bool res_fit = msvm::Solver::resident_fits(o, c.f, rc);
         if (L > 1 && !res_fit) {
             later.push_back(g);

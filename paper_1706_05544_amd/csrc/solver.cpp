@@ -298,7 +298,8 @@ size_t cache_pool_trim(int device)
     return freed;
 }
 
-void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx)
+void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx,
+                bool whole)
 {
     c.slots = 0;
     if (const char* e = getenv("SVM_CACHE_BYTES"))  // developer override
@@ -323,7 +324,7 @@ void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx)
     // a working set reads up to kMaxQ slots and the replacement needs a
     // free one besides them
     if (slots <= kMaxQ && slots < n) return;
-    if (slots < 2) return;
+    if (slots < 2 || (whole && slots < n)) return;
     // (+16 floats: the row kernel reads whole 16-row tiles, up to 15 rows
     // past the last sample, and the last row has nothing after it; with all
     // rows in the cache one more, the row of zeros of k_resident)

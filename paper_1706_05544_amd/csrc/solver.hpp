@@ -123,8 +123,10 @@ struct RowCache {
 // kernel matrix if it fits a quarter of the free device memory, else a
 // quarter of it, at most 8 GiB; the device's idle kept block counts as
 // free), > 0 = at most that many bytes (clamped likewise), < 0 = no cache.
-// Leaves slots = 0 when fewer rows than a working set needs would fit.
-void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx);
+// Leaves slots = 0 when fewer rows than a working set needs would fit, or
+// (whole) when not all of K would.
+void cache_init(RowCache& c, int64_t n, int64_t bytes, Context& cx,
+                bool whole = false);
 
 // The device and stream of one call.
 struct Context {

@@ -36,6 +36,18 @@ def _same_ovr(m1, m2, n_classes):
             assert f1[k] == f2[k], (c, k, f1[k], f2[k])
 
 
+def test_lockstep_keeps_no_cache_it_does_not_use():
+    # a budget below the whole K leaves the folds to lockstep, without a cache
+    w = workloads.make("C1", n=3000, n_test=4)
+    kw = dict(k=4, C=w.C, gamma=w.gamma, tol=w.tol, max_iter=20,
+              cache_bytes=3000 * 3000 * 2)
+    nv.svm_cache_release(-1)
+    nv.svm_cross_validate(w.X, w.y, lockstep=4, **kw)
+    assert nv.svm_cache_release(-1) == 0
+    nv.svm_cross_validate(w.X, w.y, **kw)  # one after another: with one
+    assert nv.svm_cache_release(-1) > 0
+
+
 @pytest.mark.parametrize("lockstep", [2, 4])
 def test_ovr_lockstep_equals_sequential(lockstep):
     # 784 features: at most two problems per pass; lockstep = 4 is clamped
