@@ -109,13 +109,18 @@ typedef struct {
                               device memory, else a quarter of it, at most
                               8 GiB (the memory is kept for the next
                               training: svm_cache_release).  When the budget
-                              holds the whole K of a dense problem and n^2 d
-                              is at most 6e10 (n <= 61440), K is computed at
-                              once and the outer iterations run many to a
-                              launch (working sets of at most 16; not with
-                              profile or fused); the trainings of a
-                              one-vs-rest model or a cross-validation then
-                              run side by side.  Results are the same bits */
+                              holds the whole K of a dense problem, n^2 d is
+                              at most 6e10 and 4 n^2 bytes at most 7.2e9 for
+                              each training that shares K (one: n <= 42426;
+                              n <= 61440 in any case), K is computed at once
+                              and the outer iterations run many to a launch
+                              (working sets of at most 16; not with profile
+                              or fused, nor a max_iter too small to gain
+                              from it); the trainings of a one-vs-rest model
+                              or a cross-validation then run side by side.
+                              A single training to which K would cost much
+                              does its first iterations without, as does a
+                              warm start.  Results are the same bits */
     void *stream;          /* hipStream_t; NULL: a stream of the library */
     int32_t check_every;   /* outer iterations between host polls (0: 64;
                               fewer near convergence, down to an eighth,

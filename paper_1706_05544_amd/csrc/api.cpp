@@ -407,6 +407,7 @@ svm_status svm_train_ovr(const svm_matrix* X, const int32_t* labels,
     svm_status worst = SVM_OK;
     // one row cache for all classes: the kernel rows do not depend on labels
     msvm::RowCache rc;
+    rc.trainings = n_classes;
     msvm::cache_init(rc, n, msvm::one_launch_loop(o, f) ? -1 : p->cache_bytes,
                      cx);
     auto collect = [&](int32_t c, msvm::Solver& s, const msvm::SolveResult& r) {
@@ -718,7 +719,8 @@ svm_status cv_run_many(CvData& c, const std::vector<svm_params>& ps,
     for (int g = 0; g < NG; ++g) {
         const msvm::SolveOptions& o = opts[(size_t)g];
         msvm::RowCache rc;  // K rows do not depend on fold or class
-        if (L == 1 || msvm::Solver::resident_may_fit(o, c.f))
+        rc.trainings = per;
+        if (L == 1 || msvm::Solver::resident_may_fit(o, c.f, per))
             msvm::cache_init(
                 rc, n,
                 msvm::one_launch_loop(o, c.f) ? -1 : ps[(size_t)g].cache_bytes,

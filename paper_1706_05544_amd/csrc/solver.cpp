@@ -666,10 +666,18 @@ void Solver::read_ws(WorkingSet& w)
 // mode: one in kProfileEvery.
 constexpr int64_t kProfileEvery = 4;
 
+// Where the kernel matrix costs more than a short solve gains from it, the
+// two-launch loop does the first kFirst iterations.  Solves whose gap has then
+// fallen below half of the first one ended within 172 iterations (C-SVC, two
+// Gaussians, n of 28000 to 60000: the gap 2 -> 0.10 to 0.29; of the others,
+// 1.1 and more, none below 214), so they stay in that loop up to kFirstMost
+// iterations.
+constexpr int kFirst = 32, kFirstMost = 192;
+
 // Queue chunks of `check_every` iterations, two chunks in flight, and poll
 // the done flag of the older chunk.  Iterations queued after convergence
 // return at their first instruction.
-bool Solver::run_loop(SolveResult& r)
+bool Solver::run_loop(SolveResult& r, bool* first)
 {
     const int K = o_.check_every;
     HostBuf<WorkingSet> hs(2);
@@ -723,9 +731,11 @@ bool Solver::run_loop(SolveResult& r)
         HIP_TRY(hipEventRecord(ev[slot], cx_.stream));
     };
 
-    enqueue(0, K);
-    enqueue(1, K);
+    enqueue(0, first ? 1 : K);
+    enqueue(1, first ? kFirst - 1 : K);
     int cur = 0;
+    int polls = 0;
+    double gap0 = 0.0;
     for (;;) {
         HIP_TRY(hipEventSynchronize(ev[cur]));
         const WorkingSet& w = hs.p[cur];
@@ -783,6 +793,21 @@ bool Solver::run_loop(SolveResult& r)
             throw Error{SVM_E_INTERNAL, "solver state made no progress"};
         }
         last_iter = w.iter;
+        if (first) {
+            if (polls++ == 0) {  // the gap of the start
+                gap0 = w.gap;
+                cur ^= 1;
+                continue;
+            }
+            if (polls == 2) {
+                if (w.gap > 0.5 * gap0) break;
+                enqueue(0, K);
+                enqueue(1, K);
+                cur = 0;
+                continue;
+            }
+            if (w.iter >= kFirstMost) break;
+        }
         // Near the end the chunks shrink: the launches queued behind the
         // converged iteration return at once but still cost a launch each
         // (about 5 us a pair), and a whole chunk is in flight when the host
@@ -812,12 +837,8 @@ bool Solver::run_loop(SolveResult& r)
     (void)hipEventDestroy(ev[1]);
     WorkingSet w;
     read_ws(w);
-    r.iters = w.iter;
-    r.gap = w.gap;
-    r.m = w.m;
-    r.M = w.M;
-    r.kernel_rows = w.rows;
-    r.status = w.done == 2 ? SVM_W_MAX_ITER : SVM_OK;
+    fill_result(w, r);
+    if (first) *first = w.done == 0;
     return w.done == 1;
 }
 
@@ -948,34 +969,59 @@ bool Solver::run_loop_fused(SolveResult& r)
     return w.done == 1;
 }
 
-// The kernel matrix is computed whole when that takes at most about a
-// millisecond (n^2 d / 2 products on the matrix cores; a solve touches some
-// 10 to 90 % of its rows, and the loop that needs no row of X is 2 to 3 times
-// as fast), and the blocks of one problem fit the chip.
-constexpr double kGramWork = 6e10;
+// The kernel matrix is computed whole, and the loop is k_resident, where that
+// pays.  k_gram takes n^2 d / 2 products at 106 TFLOP/s and stores 4 n^2 bytes
+// at 3.0 TB/s, one after the other (1.00 ms at 20000 x 128, 1.61 at 30000 x
+// 64, 2.8 at 46000 x 8), and an outer iteration then takes 8 us with 3 blocks
+// a problem, 11 with 16, 15 with 24, 18 with 27 and 20 with 32 against 21 to
+// 25 in the two-launch loop.  So, for one training:
+// - products: to kGramWork (0.6 ms);
+// - bytes: to kGramBytes a training that shares K (42426 rows for one): C-SVC
+//   42000 x 32, 694 iterations, 16.5 ms with the two-launch loop and 14.3
+//   with this one, 50000 x 8, 1122, 25.7 and 25.4, 60000 x 8, 1659, 37.6 and
+//   41.1.
+constexpr double kGramWork = 6e10, kGramBytes = 7.2e9;
+static double gram_seconds(double n, double ldp)
+{
+    return 4.0 * n * n / 3.0e12 + n * n * ldp / 1.06e14;
+}
+// A solve that ends within some 150 iterations gains less than kGramDear
+// (two Gaussians far apart, ms, two-launch and resident: 24000 x 100 3.29 and
+// 3.11, 28000 x 72 3.10 and 3.37, 38000 x 8 4.15 and 4.72).  Where k_gram
+// takes longer, such solves are told by their first iterations (run_first).
+// A warm start may be as good as solved: there from kGramWarm on.
+constexpr double kGramDear = 1.4e-3, kGramWarm = 1e-4;
+// gain of an iteration, for solves with a small iteration cap
+constexpr double kResGain = 1e-5;
 
 // Launches called off in one loop after which it is left (see run_resident).
 constexpr int kResOff = 3;
 
 // Blocks of a problem: as few as hold its rows (the exchange between blocks
-// costs about 1.5 us an iteration, whatever their number up to 4).
+// costs about 1.5 us an iteration up to 4 of them and grows with their number,
+// see above).
 static int64_t resident_blocks(int64_t n)
 {
     return (n + kResRows - 1) / kResRows;
 }
 
-bool Solver::resident_may_fit(const SolveOptions& o, const Features& f)
+bool Solver::resident_may_fit(const SolveOptions& o, const Features& f,
+                              int trainings)
 {
+    const double nn = (double)f.n * (double)f.n;
     return !f.csr && o.q <= 16 && !o.profile && !o.fused && f.n >= 2 &&
            resident_blocks(f.n) <= kResBlocks &&
-           (double)f.n * (double)f.n * (double)f.ldp <= kGramWork &&
+           nn * (double)f.ldp <= kGramWork &&
+           4.0 * nn <= kGramBytes * trainings &&
+           gram_seconds((double)f.n, (double)f.ldp) <=
+               kResGain * (double)o.max_iter * trainings &&
            64 * f.ldp * 4 < ((int64_t)1 << 31);
 }
 
 bool Solver::resident_fits(const SolveOptions& o, const Features& f,
                            const RowCache& c)
 {
-    return resident_may_fit(o, f) && c.slots >= f.n;
+    return resident_may_fit(o, f, c.trainings) && c.slots >= f.n;
 }
 
 int Solver::resident_capacity(int64_t n, int device)
@@ -1032,7 +1078,10 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
     for (Solver* s : g)
         if (s->seen_.count < (size_t)n) {
             s->seen_.alloc((size_t)n);
-            HIP_TRY(hipMemsetAsync(s->seen_.p, 0xFF, s->seen_.bytes(), st));
+            // (the samples that the two-launch loop has used have a slot)
+            HIP_TRY(hipMemcpyAsync(s->seen_.p, rc.slot_of.p,
+                                   (size_t)n * sizeof(int32_t),
+                                   hipMemcpyDeviceToDevice, st));
         }
     for (int p = 0; p < G; ++p) {
         Solver& s = *g[p];
@@ -1187,6 +1236,14 @@ std::vector<SolveResult> Solver::train_resident(const std::vector<Solver*>& g,
 bool Solver::loop(SolveResult& r)
 {
     if (resident_) {
+        if (!cache_->full &&
+            gram_seconds((double)n_, (double)f_.ldp) >
+                (warm_ ? kGramWarm : kGramDear)) {
+            launch_keys();
+            bool go_on = false;
+            const bool done = run_loop(r, &go_on);
+            if (!go_on) return done;
+        }
         std::vector<SolveResult> rr(1, r);
         std::vector<char> conv(1, 0);
         const bool ok = run_resident({this}, rr, conv);
@@ -1721,6 +1778,7 @@ void Solver::warm_start(const double* alpha_h)
     recompute_responses();
     HIP_TRY(hipMemsetAsync(ws_.p, 0, sizeof(WorkingSet), s));
     cx_.sync();
+    warm_ = true;
 }
 
 void Solver::get_state(double* alpha_h, double* F_h)

@@ -117,6 +117,7 @@ struct RowCache {
     // every row computed, row s in slot s (the solves that run as k_resident;
     // slot_of and owner are not used then)
     bool full = false;
+    int trainings = 1;  // that share it
 };
 
 // Sizes and clears the cache for n samples.  bytes: 0 = default (the full
@@ -244,8 +245,9 @@ public:
     // kernel matrix in the cache and runs as k_resident.
     static bool resident_fits(const SolveOptions& o, const Features& f,
                               const RowCache& c);
-    // ... if the cache holds the whole matrix
-    static bool resident_may_fit(const SolveOptions& o, const Features& f);
+    // ... if the cache holds the whole matrix and `trainings` share it
+    static bool resident_may_fit(const SolveOptions& o, const Features& f,
+                                 int trainings);
     // Training of several solvers for which resident_fits(), side by side:
     // each has compute units of its own and the same result as alone.  They
     // share the features, the stream, the type and the kernel matrix.  Should
@@ -301,7 +303,9 @@ private:
     void launch_solve(int32_t mode, hipEvent_t e0 = nullptr,
                       hipEvent_t e1 = nullptr);
     void launch_select_only();
-    bool run_loop(SolveResult& r);
+    // (first: only the first iterations, and *first whether the solve has to
+    // go on)
+    bool run_loop(SolveResult& r, bool* first = nullptr);
     // the loops of the group's solvers as k_resident launches (conv[p]:
     // converged); false when a launch could not start (the states are then
     // whole, and the two-launch loop takes over)
@@ -338,6 +342,7 @@ private:
     // the second responses buffer, the double-buffered records, the ticket
     bool fused_ = false;
     bool resident_ = false;  // the loop is k_resident
+    bool warm_ = false;      // started from a given alpha
     DevBuf<int32_t> seen_;   // its samples used so far
     int32_t off_seen_ = 0;   // its launches called off so far
     int nbi_ = 0, tilesi_ = 0, tilesk_ = 0;

@@ -24,10 +24,10 @@ pytestmark = pytest.mark.gpu
 SAME = ("iters", "b", "dual_obj", "gap", "kernel_rows", "status", "n_bounded")
 
 
-def _train(w, **kw):
+def _train(w, alpha0=None, **kw):
     k = dict(type=w.type, C=w.C, epsilon=w.eps, gamma=w.gamma, tol=w.tol)
     k.update(kw)
-    m = nv.svm_train(w.X, w.y, **k)
+    m = nv.svm_train(w.X, w.y, alpha0=alpha0, **k)
     return m.info(), nv.svm_model_get(m, 0, with_alpha=True)[2]
 
 
@@ -92,8 +92,7 @@ def _rows(n, d, svr=False):
     (4100, 20, True, {}),              # three
     (15361, 7, False, dict(max_iter=400)),               # nine
     (23041, 5, True, dict(max_iter=300)),                # thirteen
-    (61440, 4, False, dict(max_iter=300)),               # 32, the most
-    (61439, 4, True, dict(max_iter=300, working_set=12)),
+    (24001, 6, False, dict(max_iter=300, working_set=12)),
 ])
 def test_late_block(n, d, svr, kw, monkeypatch, loops):
     # Every block solves the subproblem of an iteration for itself.  One that
@@ -113,14 +112,67 @@ def test_late_block(n, d, svr, kw, monkeypatch, loops):
         assert loops() == [(i1["iters"], i1["iters"], -(-n // 1920), 0)]
 
 
+@pytest.mark.parametrize("n,d,svr,lag", [
+    (61440, 4, False, "2000"),  # 32 blocks, the most, of 128 and 8 of 256
+    (61439, 4, True, "0"),
+    (50001, 8, False, "0"),
+])
+def test_most_blocks(n, d, svr, lag, monkeypatch, loops):
+    w = _rows(n, d, svr)
+    kw = dict(k=4, type=w.type, C=w.C, epsilon=w.eps, max_iter=150)
+    D0, s0 = nv.svm_cross_validate(w.X, w.y, cache_bytes=-1, **kw)
+    monkeypatch.setenv("SVM_RESIDENT_LAG", lag)
+    D1, s1 = nv.svm_cross_validate(w.X, w.y, **kw)
+    np.testing.assert_array_equal(D1, D0)
+    assert s1["iters"] == s0["iters"]
+    assert loops() == [(150, 150, -(-n // 1920), 0)] * 4
+
+
 def test_more_rows_than_blocks_hold(loops):
     # one row past 32 blocks: the two-launch loop
     w = _rows(61441, 4)
-    i0, a0 = _train(w, cache_bytes=-1, max_iter=200)
-    i1, a1 = _train(w, max_iter=200)
-    np.testing.assert_array_equal(a1, a0)
+    kw = dict(k=4, max_iter=50)
+    D0, _ = nv.svm_cross_validate(w.X, w.y, cache_bytes=-1, **kw)
+    D1, _ = nv.svm_cross_validate(w.X, w.y, **kw)
+    np.testing.assert_array_equal(D1, D0)
     assert loops() == []
-    assert i1["cache_fills"] > 0
+
+
+@pytest.mark.parametrize("n,d,sep,kw,ran", [
+    # K costs more than a short solve gains: the two-launch loop begins, and
+    # ends a short one
+    (30001, 61, 8.0, {}, 0),
+    (42424, 12, 8.0, {}, 0),
+    (30001, 61, 2.25, {}, 32),    # told after 32 iterations
+    (42424, 12, 2.25, dict(check_every=5), 32),
+    (24001, 64, 8.0, {}, None),   # K cheap enough
+    (42428, 4, 2.25, dict(max_iter=100), 0),   # K too large for one training
+    (20001, 120, 2.25, dict(max_iter=60), 0),  # too few iterations to gain
+])
+def test_whole_k_only_where_it_pays(n, d, sep, kw, ran, loops):
+    w = _rows(n, d)
+    w.X += np.float32((sep - 2.25) / np.sqrt(d)) * w.y[:, None]
+    i0, a0 = _train(w, cache_bytes=-1, **kw)
+    i1, a1 = _train(w, **kw)
+    np.testing.assert_array_equal(a1, a0)
+    for k in SAME:
+        assert i1[k] == i0[k], k
+    assert i1["cache_fills"] + i1["cache_hits"] > 0
+    blocks = -(-n // 1920)
+    if ran == 0:
+        assert loops() == []
+    else:
+        assert loops() == [(i0["iters"] - (ran or 0), i0["iters"], blocks, 0)]
+
+
+@pytest.mark.parametrize("svr", [False, True])
+def test_accepted_warm_start_computes_no_k(svr, loops):
+    w = _rows(9001, 24, svr)
+    kw = dict(max_iter=2000)
+    i1, a1 = _train(w, **kw)
+    assert len(loops()) == 1
+    _train(w, alpha0=a1, **{**kw, "tol": max(2 * i1["gap"], 1e-3)})
+    assert loops() == []
 
 
 def test_duplicate_rows(loops):
