@@ -49,7 +49,7 @@ struct WorkingSet {
     int32_t done;      // 0 running, 1 converged (gap <= tol), 2 iteration cap
     int32_t nB;        // variables in B
     int32_t nS;        // distinct samples of B (slots)
-    int32_t called_off; // k_resident launches that did not start
+    int32_t ahead_off; // 1: no rows computed ahead in the next iteration
     int64_t iter;      // outer iterations performed
     int64_t rows;      // kernel rows evaluated (sum of nS)
     double gap, m, M;
@@ -60,7 +60,9 @@ struct WorkingSet {
     double coef[kMaxQ];   // change of the expansion coefficient per slot
     double alphaB[kMaxQ]; // new alpha_B (written by the solve)
     int32_t steps;        // inner steps of the last subproblem
-    int32_t res_launches; // k_resident launches that started
+    int32_t called_off;   // k_resident launches that did not start
+    int32_t res_launches; // ... that did
+    int32_t pad1;
     int64_t res_iters;    // outer iterations they did
     int64_t inner_total;  // inner steps summed over iterations
     int64_t rescans;      // iterations that rescanned exhausted blocks
@@ -81,6 +83,8 @@ struct WorkingSet {
     float colq[kMaxQ];        // its squared norm
     int64_t cache_served;     // kernel rows read from the cache
     int64_t cache_filled;     // kernel rows written to the cache
+    int64_t served_whole;     // of cache_served: working sets served entirely
+    int64_t filled_ahead;     // of cache_filled: rows computed ahead
     uint8_t path_log[kPathLog];  // path of iteration t at [t % kPathLog]
     uint8_t fill_log[kPathLog];  // rows written to the cache by iteration t
     uint8_t ns_log[kPathLog];    // distinct samples of iteration t

@@ -47,7 +47,9 @@ __device__ __forceinline__ void var_scores(const SelArgs& a, int64_t t,
 
 // entries per side ranked past the working set for the row cache
 constexpr int kSpec = 24;
-constexpr int64_t kSpecX = (int64_t)1 << 24;  // floats of X from which on
+// from this many floats of X on, and for so many iterations at least
+constexpr int64_t kSpecX = 32000000;
+constexpr int kSpecTry = 64;
 
 // Features per LDS slice of the working-set rows in k_select.
 int select_slice(int nblk_cols, int64_t ldp)
@@ -120,6 +122,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     WorkingSet* ws = a.ws;
     // (SS_CHECK_DONE) ws->done is tested once the record loads are in flight
     const int32_t done0 = (a.mode & SS_CHECK_DONE) ? ws->done : 0;
+    const int32_t ahead_off = ws->ahead_off;
     const uint64_t t_start = wall_clock64();
 
     constexpr int NW = kSelThreads / 64;
@@ -150,7 +153,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     __shared__ int32_t shNB, shNS, shGo, shDone;
     // the columns that the row kernel computes (see WorkingSet)
     __shared__ int32_t shCol[kMaxQ], shCs[kMaxQ], shHs[kMaxQ];
-    __shared__ int32_t shPath, shFill, shHit;
+    __shared__ int32_t shPath, shFill, shHit, shAhead;
     __shared__ int64_t shClk;
     __shared__ int32_t shNoList;       // CSR: a slot's row is longer than LM
     __shared__ int32_t shLen[kMaxQ];   // CSR: nonzeros of each slot's row
@@ -167,10 +170,19 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // the order of the keys) are computed in the columns of samples that are
     // cached already, where a launch streams X anyway: the lists are ranked
     // kSpec entries further for them.
+    // The longer lists cost 3 us an iteration, so they end after kSpecTry
+    // iterations unless a 32nd of the rows used so far belonged to working
+    // sets served entirely from the cache (at 64 iterations 0.06 to 0.62 of
+    // them in solves that gain, 0.00 in others: eps-SVR 68971 x 501, 91 ms
+    // without and 98 with them all along; C-SVC 140000 x 240, 94 and 99).  A
+    // cache with fewer slots than samples must not lose rows to them: once it
+    // has been filled as often as it has slots, they need a fourth (68971 x
+    // 501, ms, none and always: 500 slots 23.8 and 25.9, 1000 slots 23.7 and
+    // 24.6, 2000, where nothing is replaced, 20.6 and 19.4).  Decided at the
+    // end of the iteration before.
     const bool spec = NBLK == 1 && a.cache_slots > 0 && !CSR && !given &&
                       (a.mode & SS_SOLVE) && a.slice >= ((ldp + 15) & ~15) &&
-                      a.nb >= 256 && n * ldp >= kSpecX;
-    const int want = spec ? min(half + kSpec, kMaxHalf) : half;
+                      a.nb >= 256 && n * ldp >= kSpecX && !ahead_off;
     // (1) the candidate records of the row groups (best two up keys, best
     // two low keys, their variables): thread t loads records t, t +
     // kSelThreads, ... with 16-byte loads, issued before anything else
@@ -199,6 +211,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         il[2 * j + 1] = ix.w;
     }
     const int64_t iter0 = ws->iter;  // issued early, used in (8)
+    const int want = spec ? min(half + kSpec, kMaxHalf) : half;
     // Counters: read now and written back once by thread 0 at the exit, so
     // that no read-modify-write of global memory waits on the way.  Global
     // stores are likewise left to the exit: a barrier after a store waits
@@ -221,11 +234,15 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // round trip overlaps the records'.
     const bool use_cache =
         a.cache_slots > 0 && (a.mode & SS_SOLVE) && !given && wave == 1;
-    int64_t clk0 = 0, c_served = 0, c_filled = 0;
+    int64_t clk0 = 0, c_served = 0, c_filled = 0, c_whole = 0, c_ahead = 0;
+    int64_t c_used = 0;
     if (use_cache) clk0 = *a.clock;
     if (wave == 1) {
         c_served = ws->cache_served;
         c_filled = ws->cache_filled;
+        c_whole = ws->served_whole;
+        c_ahead = ws->filled_ahead;
+        c_used = ws->rows;
     }
     // (7) prefetch (dense input): waves 1.. stage the first feature slice
     // of the winners' rows in LDS, row c for candidate c, and their norms,
@@ -841,18 +858,18 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // Its path: a working set whose samples are all cached is served from
     // the cache; otherwise the missing rows are computed and go to it.  Rows
     // stop going to a cache that serves almost nothing (a working set whose
-    // samples rarely all recur): the fills cost HBM writes and the two paths
-    // give the same bits.  A cache with a slot for every sample never
+    // samples rarely all recur; rows computed ahead left out): the fills cost
+    // HBM writes and the two paths give the same bits.  A cache with a slot for every sample never
     // evicts, so it keeps filling: every working set whose samples have all
     // been used before is then served.
     if (wave == 1) {
-        int path = PATH_STREAM, nfill = 0, nhit = 0;
+        int path = PATH_STREAM, nfill = 0, nhit = 0, nahead = 0;
         int32_t cslot = -1, hsrc = -1;
         int32_t col = lane < nS ? shS[lane] : -1;
         if (use_cache) {
             const bool miss = lane < nS && hslot < 0;
             const bool fill = a.cache_slots >= a.n || iter0 < 512 ||
-                              c_served * 8 >= c_filled;
+                              c_whole * 8 >= c_filled - c_ahead;
             if (__ballot(miss) == 0) {
                 path = PATH_CACHED;
                 cslot = lane < nS ? hslot : -1;
@@ -888,6 +905,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
                 }
                 const unsigned long long fillm = __ballot(fills);
                 nfill = __popcll(fillm);
+                nahead = nfill - __popcll(__ballot(miss));
                 int64_t clk = clk0;
                 if (a.cache_slots >= a.n) {
                     // never wraps: a sample takes a slot once
@@ -918,6 +936,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
             shPath = path;
             shFill = nfill;
             shHit = nhit;
+            shAhead = nahead;
         }
     }
 
@@ -1230,6 +1249,14 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
                 ws->hit_log[t] = (uint8_t)nhit;
                 ws->cache_served = c_served + (path == PATH_CACHED ? nS : nhit);
                 ws->cache_filled = c_filled + nfill;
+                const int64_t whole = c_whole + (path == PATH_CACHED ? nS : 0);
+                const int64_t used = c_used + nS;
+                ws->served_whole = whole;
+                ws->filled_ahead = c_ahead + shAhead;
+                ws->ahead_off =
+                    (iter0 + 1 >= kSpecTry && 32 * whole < used) ||
+                    (a.cache_slots < n && c_filled + nfill >= a.cache_slots &&
+                     4 * whole < used);
             }
         }
         if (CSR && a.xsc) {

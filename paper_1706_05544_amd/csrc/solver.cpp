@@ -1419,14 +1419,16 @@ void Solver::finish(SolveResult& r, bool conv, hipEvent_t t0, int max_passes)
         } else if (atoi(e) > 0 && w.prof[4] > 0) {
             const double k = 10.0 / (double)w.prof[4];  // 100 MHz ticks -> ns
             fprintf(stderr,
-                    "[mi355svm] iters=%lld rows=%lld (cache: served %lld "
-                    "filled %lld) inner=%.1f/iter rescans=%lld slow=%lld "
+                    "[mi355svm] iters=%lld rows=%lld (cache: served %lld, %lld "
+                    "of them whole sets, filled %lld, %lld of them ahead) "
+                    "inner=%.1f/iter rescans=%lld slow=%lld "
                     "select(us): merge %.2f (bound %.2f rank %.2f groups "
                     "%.2f rescans %.2f) kss %.2f (build %.2f stage %.2f) "
                     "inner %.2f write %.2f; rows kernel %.2f us/launch "
                     "(%lld timed), cached %.2f us/launch (%lld)\n",
                     (long long)w.iter, (long long)w.rows,
-                    (long long)w.cache_served, (long long)w.cache_filled,
+                    (long long)w.cache_served, (long long)w.served_whole,
+                    (long long)w.cache_filled, (long long)w.filled_ahead,
                     (double)w.inner_total / (double)w.prof[4],
                     (long long)w.rescans, (long long)w.slow_selects,
                     1e-3 * k * w.prof[0], 1e-3 * k * w.prof[5],

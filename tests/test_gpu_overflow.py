@@ -49,14 +49,14 @@ def test_rows_computed_ahead():
     # working sets are ranks 1 and 2 of each side, then 3 and 4.  The huge row
     # has rank 8 of its side, so the first launch computes its row ahead in a
     # column past the working set, and the ordinary one rank 3 of the other.
-    n, d = 40009, 420
+    n, d = 70009, 460
     rng = np.random.default_rng(1)
     X = rng.standard_normal((n, d), dtype=np.float32)
     X[:, 0] = 0.0
     z = rng.uniform(-1, 1, n).astype(np.float32)
     # (far apart: a block of rows reports its best two only)
-    top = 100 + 1000 * np.arange(10)
-    low = 20100 + 1000 * np.arange(10)
+    top = 100 + 2000 * np.arange(10)
+    low = 35100 + 2000 * np.arange(10)
     z[top] = 100.0 - np.arange(10)
     z[low] = -100.0 + np.arange(10)
     huge, other = top[7], low[2]

@@ -1,6 +1,6 @@
 """Rows computed ahead for the kernel-row cache, and candidate records by wave.
 
-Where X is large (2^24 floats and more) the columns of a streaming launch
+Where X is large (3.2e7 floats and more) the columns of a streaming launch
 that belong to cached samples compute rows that later working sets are
 likely to need, and the cached samples' rows are read.  K values are the
 same bits either way, so a training must give the bits of the one without
@@ -8,8 +8,11 @@ the cache: with a cache that keeps everything, with one so small that it
 replaces rows all along, C-SVC and eps-SVR, another kernel, working sets
 below 16, features past one LDS slice of the selection (where no row is
 computed ahead), and shapes whose row kernel runs few blocks (a record per
-wave) or many.
+wave) or many.  Rows computed ahead end where they do not lead to working
+sets served from the cache.
 """
+import re
+
 import numpy as np
 import pytest
 
@@ -51,3 +54,44 @@ def test_same_bits_with_rows_computed_ahead(n, d, rows, kw):
         assert i1[k] == i0[k], k
     assert i1["cache_fills"] > 0
     assert i1["cache_hits"] <= i1["kernel_rows"]
+
+
+def _ahead(err):
+    """(rows in working sets served entirely, rows computed ahead) of the
+    trainings whose SVM_LOG lines err holds."""
+    found = re.findall(r"(\d+) of them whole sets, filled \d+, "
+                       r"(\d+) of them ahead", err)
+    return [tuple(map(int, f)) for f in found]
+
+
+@pytest.mark.parametrize("n,d,rows,kw,ahead", [
+    (70009, 460, 0, {}, "on"),
+    (70009, 460, 90, {}, 90),               # a cache filled at once
+    (41001, 801, 0, dict(kernel=1, coef0=1.0), "on"),
+    (41001, 800, 200, dict(working_set=10), 200),
+    (70000, 461, 0, dict(type=1, C=10.0, max_iter=300), 64 * 16),
+    (39009, 799, 0, {}, None),              # too small an X
+])
+def test_rows_ahead_only_where_they_serve(n, d, rows, kw, ahead, capfd,
+                                          monkeypatch):
+    # "on": to the end; a number: at most so many, then no more
+    X, y = _data(n, d, kw.get("type") == 1)
+    cache = rows * ((n + 3) // 4 * 4) * 4
+    monkeypatch.setenv("SVM_LOG", "1")
+    capfd.readouterr()
+    got = []
+    for cb in (-1, cache):
+        m = nv.svm_train(X, y, cache_bytes=cb, **kw)
+        got.append((m.info(), nv.svm_model_get(m, 0, with_alpha=True)[2],
+                    _ahead(capfd.readouterr().err)))
+    (i0, a0, _), (i1, a1, ((whole, done),)) = got
+    np.testing.assert_array_equal(a1, a0)
+    for k in ("iters", "b", "dual_obj", "gap", "kernel_rows", "status"):
+        assert i1[k] == i0[k], k
+    if ahead == "on":
+        assert done > 0 and 4 * whole > i1["kernel_rows"]
+    elif ahead is None:
+        assert done == 0
+    else:
+        assert done <= ahead
+        assert whole < i1["kernel_rows"] // 4
