@@ -850,13 +850,18 @@ __global__ __launch_bounds__(128) void k_predict_ksum(PredictArgs a,
     }
 }
 
-int64_t predict_few_floats(int64_t nsv, int64_t m, int64_t ldp)
+int64_t predict_chain(int64_t nsv, int64_t ldp)
 {
     const int64_t nr = predict_ranges(nsv);
-    const int64_t blocks = (m + 63) / 64 * nr;
     const int64_t tiles = ((nsv + 63) / 64 + nr - 1) / nr;
+    return tiles * (4 + (ldp + 15) / 16);
+}
+
+int64_t predict_few_floats(int64_t nsv, int64_t m, int64_t ldp)
+{
+    const int64_t blocks = (m + 63) / 64 * predict_ranges(nsv);
     const int64_t kst = (nsv + 15) & ~(int64_t)15;
-    const int64_t work = tiles * (4 + (ldp + 15) / 16);
+    const int64_t work = predict_chain(nsv, ldp);
     const int64_t most = std::min(
         work << 14,
         kFewFloats * std::max<int64_t>(1, std::min<int64_t>(4, ldp / 128)));

@@ -2140,13 +2140,20 @@ void predict_device(const svm_model& mdl, Context& cx, Features& t,
 constexpr size_t kCheapAlloc = (size_t)2 << 20;
 
 // Kernel values of the path for few query rows where a call that allocates
-// them gains from it, else 0: past kCheapAlloc the allocation costs more than
+// them gains from it, else 0.  Past kCheapAlloc the allocation costs more than
 // the two kernels gain on rows of up to 128 features (300 x 128 against 6600
-// support rows 133 -> 153 us).
-static int64_t few_floats(int64_t nsv, int64_t m, int64_t ldp)
+// support rows 133 -> 153 us), and with one output and wider rows where the
+// chain of the one kernel is short: a call takes about 95 us + 20 per million
+// values there, against 45 and half a microsecond a unit of the chain (us, one
+// kernel and two: 3000 x 200 against 200 support rows 84 and 131, 4500 x 256
+// against 700 150 and 161, 3000 rows of it 149 and 136).
+static int64_t few_floats(int64_t nsv, int64_t m, int64_t ldp, int32_t n_out)
 {
     const int64_t few = predict_few_floats(nsv, m, ldp);
-    return few * 4 <= (int64_t)kCheapAlloc || ldp > 128 ? few : 0;
+    if (few * 4 <= (int64_t)kCheapAlloc) return few;
+    if (ldp <= 128) return 0;
+    return n_out > 1 || few <= (predict_chain(nsv, ldp) - 104) * 26500 ? few
+                                                                       : 0;
 }
 
 // What bounds a call of some 100 us is the host's part: allocations and the
@@ -2163,7 +2170,7 @@ void predict_in_place(const svm_model& mdl, Context& cx, const svm_matrix* X,
     hipStream_t s = cx.stream;
     const int64_t m = X->n, ldp = padded_ld(X->d);
     const float* x = static_cast<const float*>(X->values);
-    const int64_t few = few_floats(mdl.n_sv, m, ldp);
+    const int64_t few = few_floats(mdl.n_sv, m, ldp, mdl.n_out);
     auto up = [](int64_t b) { return ((size_t)b + 255) & ~(size_t)255; };
     const size_t sq_at = 256, d_at = sq_at + up(m * 4),
                  l_at = d_at + up(m * mdl.n_out * 8),
@@ -2371,7 +2378,7 @@ void predict_rows(PredictArgs a, const Features& t, hipStream_t s,
         a.sqt = t.sq.p;
         a.m = t.n;
         a.row_base = 0;
-        const int64_t few = few_floats(a.nsv, t.n, t.ldp);
+        const int64_t few = few_floats(a.nsv, t.n, t.ldp, a.n_out);
         if (few > 0) {
             DevBuf<float> kbuf((size_t)few);
             launch_predict_few(a, kbuf.p, s);

@@ -69,6 +69,33 @@ def test_batch_does_not_change_the_bits(nsv, d, kernel, n_out):
                                    atol=tol)
 
 
+@pytest.mark.parametrize("nsv,d", [
+    (200, 200),    # a short chain of tiles: one kernel from 2 MB of values on
+    (700, 256),    # ... from 3.07 million values on
+    (400, 132), (1000, 256), (1032, 256), (257, 784), (40, 140)])
+def test_medium_batches_keep_the_bits(nsv, d):
+    # the lines between the two kernels, the one kernel's tiles of 64 x 64
+    # rows and those of 128 x 128
+    X, model = _model(nsv, d, RBF, 1)
+    rng = np.random.default_rng(d)
+    big = 128 * 96 + 1
+    Xt = torch.from_numpy(rng.standard_normal((big, d), dtype=np.float32))
+    Xd = Xt.to("cuda:0")
+    D = nv.svm_predict(model, Xd)
+    for m in (1, 2520, 2622, 4360, 4370, 128 * 95, 128 * 95 + 1):
+        Dm = nv.svm_predict(model, Xd[:m].contiguous())
+        assert torch.equal(Dm, D[:m]), m
+        out = torch.full((m, 1), float("nan"), dtype=torch.float64,
+                         device="cuda:0")
+        nv.svm_predict_noalloc(model, Xd[:m].contiguous(), out)
+        assert torch.equal(out[:, 0], D[:m]), m
+    idx, cf, _ = nv.svm_model_get(model, 0)
+    ref = oracle.decision(X[idx], cf, model.info()["b"], Xt[:200].numpy(),
+                          1.0 / d)
+    tol = np.abs(cf).sum() * (d + 40) * 2.0 ** -24
+    np.testing.assert_allclose(D[:200].cpu().numpy(), ref, rtol=0, atol=tol)
+
+
 def _csr(n, d, nnz, seed):
     rng = np.random.default_rng(seed)
     cols = (np.arange(n)[:, None] * 7 + np.cumsum(
