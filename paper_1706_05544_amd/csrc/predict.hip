@@ -360,13 +360,12 @@ __global__ __launch_bounds__(256) void k_predict_ra4(PredictArgs a)
 // wide rows
 // ---------------------------------------------------------------------------
 //
-// Rows of more than kRaMaxLdp features, one output (at 128 features the
-// values and sums at the end of a step weigh too much for two waves a SIMD:
-// 20000 x 128 against 6600 support rows 389 us with k_predict_ra1, 456 here;
-// 129 features, 50001 against 3000, 631 with k_predict, 569 here).
-// Matrix-core work bounds
-// this, so the tile is as large as the registers allow at two waves a SIMD:
-// a block of four waves takes 128 query rows (32 a wave, straight from
+// Rows of more than kRaMaxLdp features, one output, many blocks or long ones
+// (at 128 features the values and sums at the end of a step weigh too much for
+// two waves a SIMD: 20000 x 128 against 6600 support rows 389 us with
+// k_predict_ra1, 456 here; 129 features, 50001 against 3000, 631 with
+// k_predict, 569 here).  Matrix-core work bounds this, so the tile is as large
+// as the registers allow at two waves a SIMD: a block of four waves takes 128 query rows (32 a wave, straight from
 // memory into the operand layout) against 128 support rows a step, staged in
 // LDS by chunks of 32 features, double-buffered, one barrier a chunk; half
 // the operand traffic per product of k_predict's 64 x 64 tiles and a fourth
@@ -382,6 +381,11 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kWideRows = 128;    // query rows and support rows of a step
 constexpr int kWideDK = 32;       // features a chunk
 constexpr int kWideSlots = kWideRows * kWideDK / 4;  // float4 of a chunk
+// Few blocks with few steps each are better off as twice as many of half the
+// size (svm_predict, us, k_predict and this: 8000 x 200 against 400 support
+// rows 110 and 118, 8000 x 256 against 700 155 and 169; at the lines, 8000 x
+// 400 against 700 246 and 242, 16000 x 256 against 400 136 and 136)
+constexpr int64_t kWideBlocks = 96, kWideChain = 330;
 
 __global__ __launch_bounds__(256, 2) void k_predict_wide(PredictArgs a)
 {
@@ -655,10 +659,14 @@ void launch_predict(const PredictArgs& a, hipStream_t s)
             k_predict_ra1<<<grid, 256, 0, s>>>(a);
         else
             k_predict_ra4<<<grid, 256, 0, s>>>(a);
-    } else if (a.n_out <= 1 && a.ldp > kRaMaxLdp && a.ldp <= kFewMaxLdp) {
+    } else if (a.n_out <= 1 && a.ldp <= kFewMaxLdp &&
+               ((a.m + kWideRows - 1) / kWideRows * a.nrange >= kWideBlocks ||
+                predict_chain(a.nsv, a.ldp) >= kWideChain)) {
         const int64_t nq = (a.m + kWideRows - 1) / kWideRows;
         k_predict_wide<<<(unsigned)((nq + 7) / 8 * 8 * a.nrange), 256, 0,
                          s>>>(a);
+    } else if (a.n_out <= 1) {
+        k_predict<1><<<grid, 256, 0, s>>>(a);
     } else if (a.n_out <= 4) {
         k_predict<4><<<grid, 256, 0, s>>>(a);
     } else if (a.n_out <= 16) {
