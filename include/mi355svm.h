@@ -117,7 +117,9 @@ typedef struct {
                               (working sets of at most 16; not with profile
                               or fused, nor a max_iter too small to gain
                               from it); the trainings of a one-vs-rest model
-                              or a cross-validation then run side by side.
+                              or a cross-validation then run side by side
+                              (each train_ms spans all of them, up to the end
+                              of its own problem's finish).
                               A single training to which K would cost much
                               does its first iterations without, as does a
                               warm start.  Results are the same bits */
@@ -223,7 +225,11 @@ typedef struct {
                               first time in this training; rows served: of
                               working sets whose samples were all used
                               before) */
-    double train_ms;       /* device time from solver start to model ready */
+    double train_ms;       /* device time from solver start to model ready;
+                              problems that train side by side (lockstep,
+                              cache_bytes) overlap in it, so the sum over
+                              the classes of a model may be several times
+                              the time that it took */
     /* profile = 1: row/update kernel launches that computed the rows from X */
     double row_kernel_ms;        /* summed kernel time */
     int64_t row_kernel_launches; /* launches included in row_kernel_ms */
