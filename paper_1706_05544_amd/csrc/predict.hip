@@ -365,13 +365,14 @@ __global__ __launch_bounds__(256) void k_predict_ra4(PredictArgs a)
 // two waves a SIMD: 20000 x 128 against 6600 support rows 389 us with
 // k_predict_ra1, 456 here; 129 features, 50001 against 3000, 631 with
 // k_predict, 569 here).  Matrix-core work bounds this, so the tile is as large
-// as the registers allow at two waves a SIMD: a block of four waves takes 128 query rows (32 a wave, straight from
-// memory into the operand layout) against 128 support rows a step, staged in
-// LDS by chunks of 32 features, double-buffered, one barrier a chunk; half
-// the operand traffic per product of k_predict's 64 x 64 tiles and a fourth
-// of its barriers.  The 32x32x2 instruction adds its products one by one in
-// feature order, as 16x16x4 does, so two of them give the same bits as one
-// step of mfma_chunk, at half the instructions.
+// as the registers allow at two waves a SIMD: a block of four waves takes 128
+// query rows (32 a wave, straight from memory into the operand layout)
+// against 128 support rows a step, staged in LDS by chunks of 32 features,
+// double-buffered, one barrier a chunk; half the operand traffic per product
+// of k_predict's 64 x 64 tiles and a fourth of its barriers.  The 32x32x2
+// instruction adds its products one by one in feature order, as 16x16x4 does,
+// so two of them give the same bits as one step of mfma_chunk, at half the
+// instructions.
 //
 // 50001 x 783 against 12002 support rows (MI355X): 10.2 ms with k_predict,
 // 8.4 ms here (112 TFLOP/s; a loop of this instruction alone sustains 138 to

@@ -424,7 +424,8 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
                     wait = false;
 #pragma unroll
                     for (int j = 0; j < J; ++j)
-                        if (use[j]) v[j] = agent_load(xb + tid + j * kSelThreads);
+                        if (use[j])
+                            v[j] = agent_load(xb + tid + j * kSelThreads);
 #pragma unroll
                     for (int j = 0; j < J; ++j)
                         wait |= use[j] && (uint32_t)(v[j] >> 32) != tag;
@@ -935,8 +936,8 @@ void launch_resident(const ResidentArgs& a, int problems, bool svr,
 {
     if (problems <= 0) return;
     const int64_t units = (a.n + 1) / 2;
-    if (a.R < 1 || a.R > kResBlocks || a.half < 1 || a.half > 8 || a.R * a.half > kResCand ||
-        (units + a.R - 1) / a.R > kResUnits)
+    if (a.R < 1 || a.R > kResBlocks || a.half < 1 || a.half > 8 ||
+        a.R * a.half > kResCand || (units + a.R - 1) / a.R > kResUnits)
         throw Error{SVM_E_INTERNAL, "bad resident launch"};
     const size_t lds = (size_t)(svr ? 26 : 17) * kResRows;
     const void* fn = svr ? (const void*)k_resident<true>

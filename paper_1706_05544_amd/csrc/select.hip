@@ -859,9 +859,9 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // the cache; otherwise the missing rows are computed and go to it.  Rows
     // stop going to a cache that serves almost nothing (a working set whose
     // samples rarely all recur; rows computed ahead left out): the fills cost
-    // HBM writes and the two paths give the same bits.  A cache with a slot for every sample never
-    // evicts, so it keeps filling: every working set whose samples have all
-    // been used before is then served.
+    // HBM writes and the two paths give the same bits.  A cache with a slot
+    // for every sample never evicts, so it keeps filling: every working set
+    // whose samples have all been used before is then served.
     if (wave == 1) {
         int path = PATH_STREAM, nfill = 0, nhit = 0, nahead = 0;
         int32_t cslot = -1, hsrc = -1;
