@@ -16,12 +16,11 @@
 // blocks.
 //
 // Measured (MI355X, us an outer iteration, two-launch loop -> this): eps-SVR
-// 4000 x 50 24.0 -> 8.2 (3 blocks), 1501 x 50 24.6 -> 6.8 (1 block); C-SVC
+// 4000 x 50 24.0 -> 8.1 (3 blocks), 1501 x 50 24.6 -> 6.8 (1 block); C-SVC
 // 20000 x 128 25.3 -> 13.3 with the 1 ms of k_gram in it (11 blocks).  Of
-// the 8.2: update and keys 1.2, bound 0.4, candidates 0.6, rank and exchange
-// 1.8 (0.2 of it alpha in the exchange), K_BB and alpha (with the working set
-// built beside it) 1.1, curvature table 0.7, 6.8 subproblem steps 1.7,
-// results 0.6.
+// the 8.1: update and keys 1.2, bound 0.4, candidates 0.6, rank and exchange
+// 1.7, K_BB and alpha (with the working set built beside it) 1.1, curvature
+// table 0.7, 6.8 subproblem steps 1.7, results 0.6.
 //
 // The working sets, the kernel values (the same matrix-core order), the
 // subproblem and the fp64 order of the update are those of the two-launch
@@ -159,9 +158,7 @@ constexpr int kRowWavesRes = kWaves - 1;  // waves that hold rows
 // lanes each (up winners, then low winners).
 constexpr int kXchFields = 5;
 constexpr int kXchBlock = kXchFields * 16;
-// words a thread takes of the exchange of kResBlocks blocks
-constexpr int kXchMost =
-    (kResBlocks * kXchBlock + kSelThreads - 1) / kSelThreads;
+static_assert(kResBlocks * 16 <= kSelThreads, "a thread a candidate");
 // candidates per side ranked by pairs (more: rounds over the block)
 constexpr int kResCand = 256;
 
@@ -248,8 +245,7 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
     __shared__ int32_t upi[8], loi[8];
     __shared__ double svk[2][kResCand];
     __shared__ int32_t svi[2][kResCand];
-    __shared__ double sva[2][kResCand];  // R > 1: alpha of exchanged ones
-    __shared__ int32_t src[2][8];        // R > 1: the winners' places there
+    __shared__ int32_t src[2][8];  // R > 1: the winners' places there
     __shared__ int32_t nsv[2];
     __shared__ double rk[2][kWaves];
     __shared__ int32_t ri[2][kWaves];
@@ -409,47 +405,27 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
                 agent_store(w + 48, tg | (uint32_t)ab);
                 agent_store(w + 64, tg | (uint32_t)(ab >> 32));
             }
-            // J words a thread, requested together
-            auto take = [&](auto words) {
-                constexpr int J = decltype(words)::value;
-                uint64_t v[J] = {};
-                bool use[J];
-#pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    const int e = tid + j * kSelThreads;
-                    use[j] = e < R * kXchBlock && (e & 15) < 2 * half;
-                }
-                bool wait;
+            // A thread a candidate; alpha is read for the winners only,
+            // beside K_BB (with all of it here, by 5 words a candidate, an
+            // iteration took 8.2 us with 3 blocks, 10.9 with 11, 12.4 with 16
+            // and 23.0 with 32; now 8.1, 10.3, 11.7 and 21.8)
+            const int b = tid >> 4, l = tid & 15;
+            if (b < R && l < 2 * half) {
+                const Glob<const uint64_t> w = xb + tid + b * (kXchBlock - 16);
+                uint64_t w0, w1, w2;
                 do {
-                    wait = false;
-#pragma unroll
-                    for (int j = 0; j < J; ++j)
-                        if (use[j])
-                            v[j] = agent_load(xb + tid + j * kSelThreads);
-#pragma unroll
-                    for (int j = 0; j < J; ++j)
-                        wait |= use[j] && (uint32_t)(v[j] >> 32) != tag;
-                } while (wait);
-#pragma unroll
-                for (int j = 0; j < J; ++j)
-                    if (use[j]) {
-                        const int e = tid + j * kSelThreads, l = e & 15;
-                        const int b = (e >> 4) / kXchFields;
-                        const int f = (e >> 4) - kXchFields * b;
-                        const int side = l >= half ? 1 : 0;
-                        const int pos = b * half + (side ? l - half : l);
-                        const uint32_t x = (uint32_t)v[j];
-                        char* to =
-                            f < 2 ? (char*)&svk[side][pos] + 4 * f
-                            : f == 2 ? (char*)&svi[side][pos]
-                                     : (char*)&sva[side][pos] + 4 * (f - 3);
-                        __builtin_memcpy(to, &x, 4);
-                    }
-            };
-            if (R * kXchBlock <= kSelThreads)
-                take(std::integral_constant<int, 1>{});
-            else
-                take(std::integral_constant<int, kXchMost>{});
+                    w0 = agent_load(w);
+                    w1 = agent_load(w + 16);
+                    w2 = agent_load(w + 32);
+                } while ((uint32_t)(w0 >> 32) != tag ||
+                         (uint32_t)(w1 >> 32) != tag ||
+                         (uint32_t)(w2 >> 32) != tag);
+                const int side = l >= half ? 1 : 0;
+                const int pos = b * half + (side ? l - half : l);
+                svk[side][pos] = __builtin_bit_cast(
+                    double, (w1 << 32) | (uint64_t)(uint32_t)w0);
+                svi[side][pos] = (int32_t)(uint32_t)w2;
+            }
             if (a.lag && blk == R - 1) {  // (developer override)
                 const uint64_t t0 = wall_clock64();
                 while (wall_clock64() - t0 < a.lag) __builtin_amdgcn_s_sleep(1);
@@ -568,14 +544,31 @@ __global__ __launch_bounds__(kSelThreads) void k_resident(ResidentArgs a)
                     const bool ok = key != -INFINITY;
                     const int32_t t = ok ? idx : 0;
                     const int32_t smp = SVR && t >= n ? t - n : t;
-                    const int low = lane >= half ? 1 : 0;
-                    const double al =
-                        !ok     ? 0.0
-                        : R > 1 ? sva[low][src[low][low ? lane - half : lane]]
-                                : All[local(t)];
                     const float zb = as_global(P.z)[smp];
                     int32_t seen = 0;
                     if (blk == 0) seen = as_global(P.seen)[smp];
+                    double al = 0.0;
+                    if (ok && R == 1) {
+                        al = All[local(t)];
+                    } else if (ok) {
+                        // the words that its block published with it
+                        const uint32_t tag = (uint32_t)(iter0 + it + 1);
+                        const int low = lane >= half ? 1 : 0;
+                        const int e = src[low][low ? lane - half : lane];
+                        const int b = e / half, k = e - b * half;
+                        const Glob<const uint64_t> w =
+                            as_global(P.xch) +
+                            ((size_t)(tag & 1u) * R + b) * kXchBlock + 48 +
+                            (low ? half + k : k);
+                        uint64_t w0, w1;
+                        do {
+                            w0 = agent_load(w);
+                            w1 = agent_load(w + 16);
+                        } while ((uint32_t)(w0 >> 32) != tag ||
+                                 (uint32_t)(w1 >> 32) != tag);
+                        al = __builtin_bit_cast(
+                            double, (w1 << 32) | (uint64_t)(uint32_t)w0);
+                    }
                     shAl[lane] = al;
                     const bool yp = SVR ? t < n : zb > 0.0f;
                     shY[lane] = yp ? 1.0f : -1.0f;

@@ -973,7 +973,7 @@ bool Solver::run_loop_fused(SolveResult& r)
 // pays.  k_gram takes n^2 d / 2 products at 106 TFLOP/s and stores 4 n^2 bytes
 // at 3.0 TB/s, one after the other (1.00 ms at 20000 x 128, 1.61 at 30000 x
 // 64, 2.8 at 46000 x 8), and an outer iteration then takes 8 us with 3 blocks
-// a problem, 11 with 16, 15 with 24, 18 with 27 and 20 with 32 against 21 to
+// a problem, 10 with 11, 12 with 16, 16 with 24 and 22 with 32 against 21 to
 // 25 in the two-launch loop.  So, for one training:
 // - products: to kGramWork (0.6 ms);
 // - bytes: to kGramBytes a training that shares K (42426 rows for one): C-SVC
