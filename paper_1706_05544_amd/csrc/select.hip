@@ -119,10 +119,11 @@ __device__ __forceinline__ int flag_exclusive_scan(int* v, int64_t L,
 template <bool SVR, int NBLK, bool CSR>
 __device__ __forceinline__ void select_body(const SelArgs& a)
 {
+    constexpr bool AHEAD = NBLK == 1 && !CSR;  // rows may be computed ahead
     WorkingSet* ws = a.ws;
     // (SS_CHECK_DONE) ws->done is tested once the record loads are in flight
     const int32_t done0 = (a.mode & SS_CHECK_DONE) ? ws->done : 0;
-    const int32_t ahead_off = ws->ahead_off;
+    const int32_t ahead_off = AHEAD ? ws->ahead_off : 0;
     const uint64_t t_start = wall_clock64();
 
     constexpr int NW = kSelThreads / 64;
@@ -180,7 +181,7 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     // 501, ms, none and always: 500 slots 23.8 and 25.9, 1000 slots 23.7 and
     // 24.6, 2000, where nothing is replaced, 20.6 and 19.4).  Decided at the
     // end of the iteration before.
-    const bool spec = NBLK == 1 && a.cache_slots > 0 && !CSR && !given &&
+    const bool spec = AHEAD && a.cache_slots > 0 && !given &&
                       (a.mode & SS_SOLVE) && a.slice >= ((ldp + 15) & ~15) &&
                       a.nb >= 256 && n * ldp >= kSpecX && !ahead_off;
     // (1) the candidate records of the row groups (best two up keys, best
@@ -240,9 +241,11 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
     if (wave == 1) {
         c_served = ws->cache_served;
         c_filled = ws->cache_filled;
-        c_whole = ws->served_whole;
-        c_ahead = ws->filled_ahead;
-        c_used = ws->rows;
+        if (AHEAD) {
+            c_whole = ws->served_whole;
+            c_ahead = ws->filled_ahead;
+            c_used = ws->rows;
+        }
     }
     // (7) prefetch (dense input): waves 1.. stage the first feature slice
     // of the winners' rows in LDS, row c for candidate c, and their norms,
@@ -869,7 +872,8 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
         if (use_cache) {
             const bool miss = lane < nS && hslot < 0;
             const bool fill = a.cache_slots >= a.n || iter0 < 512 ||
-                              c_whole * 8 >= c_filled - c_ahead;
+                              (AHEAD ? c_whole : c_served) * 8 >=
+                                  c_filled - c_ahead;
             if (__ballot(miss) == 0) {
                 path = PATH_CACHED;
                 cslot = lane < nS ? hslot : -1;
@@ -1249,14 +1253,18 @@ __device__ __forceinline__ void select_body(const SelArgs& a)
                 ws->hit_log[t] = (uint8_t)nhit;
                 ws->cache_served = c_served + (path == PATH_CACHED ? nS : nhit);
                 ws->cache_filled = c_filled + nfill;
-                const int64_t whole = c_whole + (path == PATH_CACHED ? nS : 0);
-                const int64_t used = c_used + nS;
-                ws->served_whole = whole;
-                ws->filled_ahead = c_ahead + shAhead;
-                ws->ahead_off =
-                    (iter0 + 1 >= kSpecTry && 32 * whole < used) ||
-                    (a.cache_slots < n && c_filled + nfill >= a.cache_slots &&
-                     4 * whole < used);
+                if (AHEAD) {
+                    const int64_t whole =
+                        c_whole + (path == PATH_CACHED ? nS : 0);
+                    const int64_t used = c_used + nS;
+                    ws->served_whole = whole;
+                    ws->filled_ahead = c_ahead + shAhead;
+                    ws->ahead_off =
+                        (iter0 + 1 >= kSpecTry && 32 * whole < used) ||
+                        (a.cache_slots < n &&
+                         c_filled + nfill >= a.cache_slots &&
+                         4 * whole < used);
+                }
             }
         }
         if (CSR && a.xsc) {
