@@ -1,6 +1,6 @@
 """Rows computed ahead for the kernel-row cache, and candidate records by wave.
 
-Where X is large (3.2e7 floats and more) the columns of a streaming launch
+Where X is large (2^24 floats and more) the columns of a streaming launch
 that belong to cached samples compute rows that later working sets are
 likely to need, and the cached samples' rows are read.  K values are the
 same bits either way, so a training must give the bits of the one without
@@ -70,7 +70,7 @@ def _ahead(err):
     (41001, 801, 0, dict(kernel=1, coef0=1.0), "on"),
     (41001, 800, 200, dict(working_set=10), 200),
     (70000, 461, 0, dict(type=1, C=10.0, max_iter=300), 64 * 16),
-    (39009, 799, 0, {}, None),              # too small an X
+    (39009, 427, 0, {}, None),              # too small an X
 ])
 def test_rows_ahead_only_where_they_serve(n, d, rows, kw, ahead, capfd,
                                           monkeypatch):
@@ -95,3 +95,37 @@ def test_rows_ahead_only_where_they_serve(n, d, rows, kw, ahead, capfd,
     else:
         assert done <= ahead
         assert whole < i1["kernel_rows"] // 4
+
+
+@pytest.mark.parametrize("n,d,order", [
+    (29001, 784, "mixed"),   # fewer groups of records than entries of a list
+    (40009, 421, "sorted"),  # the candidates of a side in half of them
+    (64001, 421, "uneven"),  # ... in less than half
+])
+def test_few_groups_of_records(n, d, order, capfd, monkeypatch):
+    # The longer lists of candidates are cut by a bound that so many groups
+    # of records have to reach.  With fewer that hold candidates every
+    # candidate stayed, and ranking them took 15 times what it takes without
+    # rows computed ahead (with them elsewhere up to 4 times).
+    X, y = _data(n, d)
+    if order != "mixed":
+        take = np.argsort(y, kind="stable")
+        if order == "uneven":
+            take = take[:int((y < 0).sum()) + n // 6]
+        X, y = X[take], y[take]
+    monkeypatch.setenv("SVM_LOG", "1")
+    capfd.readouterr()
+    got, rank = [], []
+    for cb in (-1, 0):
+        for _ in range(2):  # (the first one warms the clocks up)
+            m = nv.svm_train(X, y, cache_bytes=cb)
+        got.append((m.info(), nv.svm_model_get(m, 0, with_alpha=True)[2]))
+        err = capfd.readouterr().err
+        rank.append(float(re.findall(r" rank ([\d.]+) groups", err)[-1]))
+        ahead = _ahead(err)
+    (i0, a0), (i1, a1) = got
+    np.testing.assert_array_equal(a1, a0)
+    for k in ("iters", "b", "dual_obj", "gap", "kernel_rows", "status"):
+        assert i1[k] == i0[k], k
+    assert ahead[-1][1] > 0
+    assert rank[1] < 8 * rank[0]
