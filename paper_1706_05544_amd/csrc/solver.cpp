@@ -671,8 +671,13 @@ constexpr int64_t kProfileEvery = 4;
 // fallen below half of the first one ended within 172 iterations (C-SVC, two
 // Gaussians, n of 28000 to 60000: the gap 2 -> 0.10 to 0.29; of the others,
 // 1.1 and more, none below 214), so they stay in that loop up to kFirstMost
-// iterations.
-constexpr int kFirst = 32, kFirstMost = 192;
+// iterations.  After kFirstLook iterations the gap of those short solves was
+// 0.27 to 0.82 of the first one and that of the others 0.92 to 1.23 (0.61 to
+// 0.65 for two eps-SVR): above kFirstFar the first iterations end there (30000
+// x 60, 506 iterations, 8.7 ms with 32 of them, 8.5 with 12, 8.25 with none;
+// 97 iterations, 3.15, 3.24 and 3.25).
+constexpr int kFirst = 32, kFirstLook = 12, kFirstMost = 192;
+constexpr double kFirstFar = 0.87;
 
 // Queue chunks of `check_every` iterations, two chunks in flight, and poll
 // the done flag of the older chunk.  Iterations queued after convergence
@@ -731,8 +736,9 @@ bool Solver::run_loop(SolveResult& r, bool* first)
         HIP_TRY(hipEventRecord(ev[slot], cx_.stream));
     };
 
+    const int look = warm_ ? kFirst : kFirstLook;
     enqueue(0, first ? 1 : K);
-    enqueue(1, first ? kFirst - 1 : K);
+    enqueue(1, first ? look - 1 : K);
     int cur = 0;
     int polls = 0;
     double gap0 = 0.0;
@@ -794,12 +800,20 @@ bool Solver::run_loop(SolveResult& r, bool* first)
         }
         last_iter = w.iter;
         if (first) {
-            if (polls++ == 0) {  // the gap of the start
+            if (polls == 0) {  // the gap of the start
+                polls = 1;
                 gap0 = w.gap;
-                cur ^= 1;
+                cur = 1;
                 continue;
             }
-            if (polls == 2) {
+            if (w.iter < kFirst) {
+                if (w.gap > kFirstFar * gap0) break;
+                enqueue(0, kFirst - look);
+                cur = 0;
+                continue;
+            }
+            if (polls == 1) {
+                polls = 2;
                 if (w.gap > 0.5 * gap0) break;
                 enqueue(0, K);
                 enqueue(1, K);
@@ -988,7 +1002,7 @@ static double gram_seconds(double n, double ldp)
 // A solve that ends within some 150 iterations gains less than kGramDear
 // (two Gaussians far apart, ms, two-launch and resident: 24000 x 100 3.29 and
 // 3.11, 28000 x 72 3.10 and 3.37, 38000 x 8 4.15 and 4.72).  Where k_gram
-// takes longer, such solves are told by their first iterations (run_first).
+// takes longer, such solves are told by their first iterations (run_loop).
 // A warm start may be as good as solved: there from kGramWarm on.
 constexpr double kGramDear = 1.4e-3, kGramWarm = 1e-4;
 // gain of an iteration, for solves with a small iteration cap

@@ -143,8 +143,8 @@ def test_more_rows_than_blocks_hold(loops):
     # ends a short one
     (30001, 61, 8.0, {}, 0),
     (42424, 12, 8.0, {}, 0),
-    (30001, 61, 2.25, {}, 32),    # told after 32 iterations
-    (42424, 12, 2.25, dict(check_every=5), 32),
+    (30001, 61, 2.25, {}, 12),    # told after 12 iterations
+    (42424, 12, 2.25, dict(check_every=5), 12),
     (24001, 64, 8.0, {}, None),   # K cheap enough
     (42428, 4, 2.25, dict(max_iter=100), 0),   # K too large for one training
     (20001, 120, 2.25, dict(max_iter=60), 0),  # too few iterations to gain
@@ -163,6 +163,29 @@ def test_whole_k_only_where_it_pays(n, d, sep, kw, ran, loops):
         assert loops() == []
     else:
         assert loops() == [(i0["iters"] - (ran or 0), i0["iters"], blocks, 0)]
+
+
+@pytest.mark.parametrize("svr,C", [(True, 10.0), (False, 0.1)])
+def test_first_iterations(svr, C, loops):
+    # the stages at which the first iterations tell a long solve: after 12 and
+    # after 32 of them
+    n, kw = 30001, dict(C=C, max_iter=600)
+    w = _rows(n, 61, svr)
+    if not svr:
+        w.X += np.float32(1.75 / np.sqrt(61)) * w.y[:, None]
+    gap = [_train(w, cache_bytes=-1, **{**kw, "max_iter": k})[0]["gap"]
+           for k in (1, 12, 32)]
+    i0, a0 = _train(w, cache_bytes=-1, **kw)
+    i1, a1 = _train(w, **kw)
+    np.testing.assert_array_equal(a1, a0)
+    for k in SAME:
+        assert i1[k] == i0[k], k
+    ran = (12 if gap[1] > 0.87 * gap[0] else
+           32 if gap[2] > 0.5 * gap[0] else 192)
+    if ran >= i0["iters"]:
+        assert loops() == []
+    else:
+        assert loops() == [(i0["iters"] - ran, i0["iters"], 16, 0)]
 
 
 @pytest.mark.parametrize("svr", [False, True])
