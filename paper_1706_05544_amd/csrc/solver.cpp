@@ -1166,7 +1166,6 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
     // the loop when that has happened kResOff times (20 ms each).
     std::vector<int32_t> off0((size_t)G);  // called off before
     for (int p = 0; p < G; ++p) off0[(size_t)p] = g[p]->off_seen_;
-    std::vector<WorkingSet> wl((size_t)G);
     bool ok = true, again = false;
     int offs = 0;
     try {
@@ -1185,12 +1184,16 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
                 if (!run || off || again) break;
                 enqueue(cur);
             }
+            // the states as the launches still queued leave them
+            for (int p = 0; p < G; ++p)
+                HIP_TRY(hipMemcpyAsync(&hw.p[p], g[p]->ws_.p,
+                                       sizeof(WorkingSet),
+                                       hipMemcpyDeviceToHost, st));
             cx.sync();
             run = false;
             for (int p = 0; p < G; ++p) {
-                g[p]->read_ws(wl[(size_t)p]);
-                run |= !wl[(size_t)p].done;
-                off0[(size_t)p] = wl[(size_t)p].called_off;
+                run |= !hw.p[p].done;
+                off0[(size_t)p] = hw.p[p].called_off;
             }
             again = off;
             if (!run) break;
@@ -1204,7 +1207,7 @@ bool Solver::run_resident(const std::vector<Solver*>& g,
         throw;
     }
     for (int p = 0; p < G; ++p) {
-        const WorkingSet& w = wl[(size_t)p];
+        const WorkingSet& w = hw.p[p];
         g[p]->fill_result(w, r[(size_t)p]);
         conv[(size_t)p] = w.done == 1;
         g[p]->off_seen_ = w.called_off;
